@@ -136,7 +136,11 @@ enum {
  *                     and score exactly every template whose bound reaches
  *                     the N-th best exact score: the same top-N as the plain
  *                     path, usually after scoring a small fraction of the
- *                     library exactly. Exclusive with the pre-filter.
+ *                     library exactly. Exclusive with the pre-filter. The
+ *                     plain path and the rescoring of a pre-filter use the
+ *                     same bounds where that is faster (no per-template
+ *                     outputs asked for, stream not being captured, scratch
+ *                     to be had): same results.
  *   rescore_policy    with a coarse scorer: TM_RESCORE_CERTIFIED (default)
  *                     or TM_RESCORE_KEEP.
  *   rescore_keep      TM_RESCORE_KEEP: fraction of the T' templates rescored
@@ -145,7 +149,11 @@ enum {
  *                     rescored from the candidate list (0 = 0.1); a pattern
  *                     whose certified set is larger is scored in full.
  *   n_rescored        optional device [B] int32 output: templates scored
- *                     exactly per pattern (T' for a full scan), or NULL.
+ *                     exactly per pattern (T' for a full scan), or NULL. With
+ *                     TM_COARSE_BOUND and NULL the library may reach the same
+ *                     top-N by other passes that form no such set (finer
+ *                     windows for the templates in question); rescore_keep
+ *                     then has no effect.
  *   compact_rows      0: polar is [B, R, n_theta]; 1: polar holds only the
  *                     library's touched rows in increasing order,
  *                     [B, n_rows, n_theta] (tm_polar_transform_rows with the
@@ -347,7 +355,10 @@ int tm_mask_from_mean(const void* patterns, tm_dtype dtype, int32_t B, int32_t H
  *                best_score and best_angle must be both NULL or both set,
  *                and are only available without pre-filter or coarse
  *                scorer.
- * Errors: TM_EINVAL, TM_EUNSUPPORTED (unknown options), TM_EHIP, TM_ENODEV. */
+ * Scratch comes from the stream-ordered allocator; the plain path does without
+ * where there is none (at most about 4 GiB of bounds at a time).
+ * Errors: TM_EINVAL, TM_EUNSUPPORTED (unknown options), TM_ENOMEM, TM_EHIP,
+ *         TM_ENODEV. */
 int tm_match_batch(const tm_library* lib, const float* polar, const double* norms,
                    const float* profiles, int32_t B, const tm_match_opts* opts, int32_t N,
                    int32_t* top_template, int32_t* top_angle, float* top_score,

@@ -103,6 +103,17 @@ constexpr int kImageExp = 14;              // window maxima scaled below 2^14
 constexpr size_t kLdsBudget = 128 * 1024;  // window image (16-bit offsets)
 constexpr int kFirst = 48;                 // best bounds scored exactly first
 constexpr int kBuildWaves = 8;             // waves that build the window image's rows
+constexpr int kParts = 1024;               // chunk ranges (waves x workgroups of a pattern)
+constexpr int64_t kSearchRecords = 8192;   // records of a plain scan from which the search pays
+constexpr int64_t kSearchWork = 3000000;   //   for a sparse library, whatever the batch (records x
+constexpr int64_t kBoundRecords = 65536;   //   patterns otherwise), and for the others
+constexpr int32_t kSearchChunk = 65536;    // patterns of a plain path's search at a time, and
+constexpr size_t kSearchScratch = size_t(4) << 30;   // the bytes of their bounds
+constexpr int kFillGrid = 512;             // workgroups that fill the chip (two per CU)
+constexpr int kRefineBatch = 128;          // largest batch of a dense library that is refined,
+constexpr int kRefineTemplates = 8192;     //   its least templates
+constexpr int64_t kRefineSpots = 24;       //   and pixels per template
+constexpr int kMaxSplit = 32;              // workgroups per pattern of a small batch
 constexpr int kMaxCols = 12;               // window columns per lane (n_theta <= 768)
 
 // ---------------------------------------------------------------- host side
@@ -200,10 +211,12 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
              const u32x4* __restrict__ recs, int rec_bytes, const int* __restrict__ chunk_end,
              const int4* __restrict__ slot_end, const int* __restrict__ part, int n_cs,
              float dfac, float* __restrict__ Qc,
-             float* __restrict__ lane_q, int32_t* __restrict__ lane_c) {
+             float* __restrict__ lane_q, int32_t* __restrict__ lane_c, float* __restrict__ amax) {
     extern __shared__ uint16_t m16[];        // window image: pairs of halves
     __shared__ float red[NW];
     const int b = blockIdx.x;
+    // gridDim.y workgroups share a pattern's chunks (a power of 2)
+    const size_t lists = (static_cast<size_t>(b) * gridDim.y + blockIdx.y) * NW * 64;
     const int lane = threadIdx.x & 63;
     const int wave = tmlib::uniform(threadIdx.x >> 6);
     const float* src = polar + static_cast<size_t>(b) * Rs * n;
@@ -211,11 +224,13 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
     const double pn = norms[b];
     // a non-finite norm: the exact scorer flags the pattern; bounds 0
     if ((__double_as_longlong(pn) & 0x7ff0000000000000LL) == 0x7ff0000000000000LL) {
-        for (int i = threadIdx.x; i < n_cs; i += NW * 64) qrow[i] = 0.0f;
+        if (blockIdx.y == 0)
+            for (int i = threadIdx.x; i < n_cs; i += NW * 64) qrow[i] = 0.0f;
         if (lane_q) {
-            lane_q[static_cast<size_t>(b) * NW * 64 + threadIdx.x] = -INFINITY;
-            lane_c[static_cast<size_t>(b) * NW * 64 + threadIdx.x] = -1;
+            lane_q[lists + threadIdx.x] = -INFINITY;
+            lane_c[lists + threadIdx.x] = -1;
         }
+        if (amax && blockIdx.y == 0 && threadIdx.x == 0) amax[b] = 0.0f;
         return;
     }
     // 1. A = max |P| over the touched rows, and the image scale; a lane
@@ -246,6 +261,7 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
     float A = red[0];
 #pragma unroll
     for (int w = 1; w < NW; ++w) A = fmaxf(A, red[w]);
+    if (amax && blockIdx.y == 0 && threadIdx.x == 0) amax[b] = A;
     int e = 0;
     (void)frexpf(A, &e);                        // A = m 2^e, m in [0.5, 1)
     const float scale = A > 0.0f ? ldexpf(1.0f, kImageExp - e) : 1.0f;
@@ -362,10 +378,12 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
     }
     const float out_scale = 1.0f / (scale * static_cast<float>(1 << kWeightExp));   // power of 2
     const uint32_t base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u16*)m16));
-    // the wave's chunks [c_begin, c_end) hold about 1/NW of the units
+    // the wave's chunks [c_begin, c_end) hold about 1 / (NW gridDim.y) of
+    // the units
     // each lane also keeps its largest bound and that bound's column (the
     // first of equal ones), optionally written out at the end
-    const int c_begin = part[wave], c_end = part[wave + 1];
+    const int fine = kParts / (NW * gridDim.y), p0 = (blockIdx.y * NW + wave) * fine;
+    const int c_begin = part[p0], c_end = part[p0 + fine];
     float best_q = -INFINITY;
     int best_c = -1;
     if (c_begin < c_end) {
@@ -490,8 +508,8 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
     if (u + 2 < u_end) process(g2, u + 2);
     }
     if (lane_q) {
-        lane_q[static_cast<size_t>(b) * NW * 64 + threadIdx.x] = best_q;
-        lane_c[static_cast<size_t>(b) * NW * 64 + threadIdx.x] = best_c;
+        lane_q[lists + threadIdx.x] = best_q;
+        lane_c[lists + threadIdx.x] = best_c;
     }
 }
 
@@ -773,17 +791,13 @@ int tmlib::bound_prepare(tm_library* L, const std::vector<std::vector<HostPixel>
         if (units >= INT32_MAX / 1024) return TM_OK;
         cend[c] = static_cast<int32_t>(units);
     }
-    // chunk ranges of the waves of an 8-wave and a 16-wave workgroup, each
-    // about 1/NW of the units (chunks are contiguous per wave)
+    // kParts chunk ranges of about equal units: a wave takes a run of them
+    // (chunks are contiguous per wave)
     std::vector<int32_t> part;
     const int64_t units = n_chunks ? cend[n_chunks - 1] : 0;
-    for (int nw : {8, 16}) {
-        for (int w = 0; w <= nw; ++w) {
-            const int64_t target = units * w / nw;
-            int32_t c = 0;
-            while (c < n_chunks && (c == 0 ? 0 : cend[c - 1]) < target) ++c;
-            part.push_back(w == nw ? n_chunks : c);
-        }
+    for (int32_t w = 0, c = 0; w <= kParts; ++w) {
+        while (c < n_chunks && (c == 0 ? 0 : cend[c - 1]) < units * w / kParts) ++c;
+        part.push_back(w == kParts ? n_chunks : c);
     }
 
     auto up = [&](auto** dst, const auto& v) -> int {
@@ -834,10 +848,33 @@ void tmlib::bound_release(tm_library* L) {
 
 // ------------------------------------------------------------ launches
 
+namespace {
+
+size_t image_bytes(const tm_library* L) {
+    return static_cast<size_t>(L->n_rows + 1) * L->bnd_L * sizeof(uint32_t);
+}
+
+// Waves per workgroup: every wave slot when the image fills the LDS.
+int bound_waves(const tm_library* L) { return image_bytes(L) > 64 * 1024 ? 16 : 8; }
+
+// Workgroups per pattern: one when the patterns alone fill the chip (two
+// workgroups per CU); for fewer, the chunks of a pattern are split, down to
+// one chunk per wave, each workgroup building the image for itself.
+int bound_split(const tm_library* L, int32_t B) {
+    int split = 1;
+    while (split < kMaxSplit && 2 * static_cast<int64_t>(split) * B <= kFillGrid &&
+           2 * split * bound_waves(L) <= L->bnd_chunks)
+        split *= 2;
+    return split;
+}
+
+}  // namespace
+
 int tmlib::bound_scores_impl(const tm_library* L, const float* polar, const double* norms,
                              int32_t B, float* out, bool template_order, bool compact,
-                             hipStream_t s, float* lane_q, int32_t* lane_c, int* n_list) {
-    const size_t image = static_cast<size_t>(L->n_rows + 1) * L->bnd_L * sizeof(uint32_t);
+                             hipStream_t s, float* lane_q, int32_t* lane_c, int split,
+                             float* amax) {
+    const size_t image = image_bytes(L);
     // window maxima over win + 4 win - n columns (see the header), at most a row
     const int n = L->n_theta, win = L->bnd_win;
     const int wlen = std::min(5 * win - n, n);
@@ -854,19 +891,16 @@ int tmlib::bound_scores_impl(const tm_library* L, const float* polar, const doub
         TM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                    hipFuncAttributeMaxDynamicSharedMemorySize,
                                    static_cast<int>(lds)));
-        hipLaunchKernelGGL(kern, dim3(B), dim3(nw * 64), lds, s, polar, norms, Rs, L->n_theta, rows,
+        hipLaunchKernelGGL(kern, dim3(B, split), dim3(nw * 64), lds, s, polar, norms, Rs, L->n_theta, rows,
                            L->d_bnd_rowat, L->n_rows, L->bnd_L, win, wlen, static_cast<int>(scr),
                            reinterpret_cast<const u32x4*>(L->d_bnd_recs),
                            static_cast<int>(L->bnd_units * 1024), L->d_bnd_end,
                            reinterpret_cast<const int4*>(L->d_bnd_slots),
-                           L->d_bnd_part + (nw == 8 ? 0 : 9), n_cs, L->bnd_dfac, Qc, lane_q,
-                           lane_c);
-        if (n_list) *n_list = nw * 64;
+                           L->d_bnd_part, n_cs, L->bnd_dfac, Qc, lane_q, lane_c, amax);
         TM_HIP(hipGetLastError());
         return TM_OK;
     };
-    // one workgroup per CU when the image fills the LDS: use every wave slot
-    const bool whole = image > 64 * 1024;
+    const bool whole = bound_waves(L) == 16;
     // n_theta = 360 (windows of 90 columns) has its own instance
     int r;
     if (L->bnd_win == 90)
@@ -891,32 +925,71 @@ int tmlib::bound_match(const tm_library* lib, const float* polar, const double* 
                        int32_t* top_angle, float* top_score, bool compact, hipStream_t s) {
     const int Tp = lib->Tp;
     const int n_cs = lib->bnd_chunks * kLanes;
-    float* Qc = nullptr;
-    float* lq = nullptr;
-    int32_t* lc = nullptr;
-    TM_HIP(hipMallocAsync(reinterpret_cast<void**>(&Qc), static_cast<size_t>(B) * n_cs * sizeof(float), s));
-    int r = TM_OK;
-    hipError_t e = hipMallocAsync(reinterpret_cast<void**>(&lq), static_cast<size_t>(B) * 1024 * sizeof(float), s);
-    if (e == hipSuccess)
-        e = hipMallocAsync(reinterpret_cast<void**>(&lc), static_cast<size_t>(B) * 1024 * sizeof(int32_t), s);
-    if (e != hipSuccess) r = tmlib::hip_fail(e, "hipMallocAsync");
-    int n_list = 0;
-    if (!r) r = bound_scores_impl(lib, polar, norms, B, Qc, false, compact, s, lq, lc, &n_list);
-    const double frac = cap_frac > 0.0 ? cap_frac : 0.1;
-    int32_t cap = static_cast<int32_t>(std::ceil(frac * Tp - 1e-9));
-    cap = std::max(N, std::min(cap, Tp));
-    // the bound ranks templates less sharply than the exact score: the 48
-    // best of the lanes' largest bounds (at most one per lane) are scored
-    // exactly first, so that the threshold starts high
-    if (!r) r = tmlib::certified_rescore(lib, polar, norms, B, N, std::max(N, kFirst), Qc, n_cs,
-                                         lib->d_bnd_tid, 0.0, cap, n_rescored, top_template,
-                                         top_angle, top_score, compact, s, lq, lc, n_list);
-    for (void* p : {static_cast<void*>(lq), static_cast<void*>(lc), static_cast<void*>(Qc)}) {
-        if (!p) continue;
-        e = hipFreeAsync(p, s);
-        if (!r && e != hipSuccess) r = tmlib::hip_fail(e, "hipFreeAsync");
+    if (lib->sr_all && !n_rescored)
+        return tmlib::search_all(lib, polar, norms, B, N, top_template, top_angle, top_score, compact, s);
+    // the certified rescoring's list holds one workgroup's lanes
+    const bool refine = lib->search && !n_rescored && B <= kRefineBatch && Tp >= kRefineTemplates &&
+                        lib->n_spots >= kRefineSpots * Tp;
+    const int split = refine ? bound_split(lib, B) : 1;
+    const int n_list = split * bound_waves(lib) * 64;
+    const size_t nl = static_cast<size_t>(B) * n_list;
+    float *Qc, *lq, *amax;
+    int32_t* lc;
+    Scratch mem;
+    mem.add(Qc, static_cast<size_t>(B) * n_cs);
+    mem.add(lq, nl);
+    mem.add(lc, nl);
+    mem.add(amax, B);
+    int r = mem.allocate(s);
+    if (!r) r = bound_scores_impl(lib, polar, norms, B, Qc, false, compact, s, lq, lc, split, amax);
+    // The rest goes by refinement of the bounds (tm_search.hip). A caller
+    // that asks for the size of the certified set gets the pass that forms
+    // one (the same top-N): the 48 best of the lanes' largest bounds (at most
+    // one per lane) are scored exactly first, so that the threshold starts
+    // high
+    if (!r && refine) {
+        r = tmlib::refine_search(lib, polar, norms, B, N, amax, Qc, n_cs, lq, lc, n_list, top_template,
+                                 top_angle, top_score, compact, s);
+    } else if (!r) {
+        const double frac = cap_frac > 0.0 ? cap_frac : 0.1;
+        int32_t cap = static_cast<int32_t>(std::ceil(frac * Tp - 1e-9));
+        cap = std::max(N, std::min(cap, Tp));
+        r = tmlib::certified_rescore(lib, polar, norms, B, N, std::max(N, kFirst), Qc, n_cs,
+                                     lib->d_bnd_tid, 0.0, cap, n_rescored, top_template, top_angle,
+                                     top_score, compact, s, lq, lc, n_list);
     }
-    return r;
+    return mem.release(s, r);
+}
+
+// The plain path's top-N by the window-bound search, where that pays and its
+// scratch can be had: patterns in chunks of bounded scratch.
+bool tmlib::search_pays(const tm_library* lib, int32_t B) {
+    if (lib->sr_all)
+        return lib->n_records >= kSearchRecords || static_cast<int64_t>(B) * lib->n_records >= kSearchWork;
+    return lib->bound && lib->n_records >= kBoundRecords;
+}
+
+int tmlib::search_top(const tm_library* lib, const float* polar, const double* norms, int32_t B,
+                      int32_t N, int32_t* top_template, int32_t* top_angle, float* top_score,
+                      bool compact, hipStream_t s) {
+    const size_t row = static_cast<size_t>(lib->bnd_chunks) * kLanes * sizeof(float);
+    const int32_t chunk = lib->sr_all ? kSearchChunk
+                                      : static_cast<int32_t>(std::max<size_t>(1, std::min<size_t>(kSearchChunk, kSearchScratch / row)));
+    const size_t pattern = static_cast<size_t>(compact ? lib->n_rows : lib->R) * lib->n_theta;
+    for (int32_t b0 = 0; b0 < B; b0 += chunk) {
+        const int32_t nb = std::min(chunk, B - b0);
+        const size_t o = static_cast<size_t>(b0) * N;
+        int r = bound_match(lib, polar + b0 * pattern, norms + b0, nb, N, 0.0, nullptr, top_template + o,
+                            top_angle + o, top_score + o, compact, s);
+        if (r == TM_ENOMEM) {
+            (void)hipGetLastError();             // no scratch: the plain scan needs none
+            tmlib::clear_error();
+            r = launch_match(lib, polar + b0 * pattern, norms + b0, nb, N, top_template + o, top_angle + o,
+                             top_score + o, nullptr, nullptr, nullptr, 0, nullptr, nullptr, compact, s);
+        }
+        if (r) return r;
+    }
+    return TM_OK;
 }
 
 // --------------------------------------------------------------- C ABI

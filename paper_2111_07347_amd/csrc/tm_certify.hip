@@ -251,7 +251,9 @@ merge_first(const int32_t* __restrict__ full, int B, const double* __restrict__ 
 constexpr int kPlanThreads = 1024;
 constexpr int kSlotBudget = 16384;       // partial lists per launch
 constexpr int kChunkCand = 512;          // candidate entries per task
-constexpr int kChunkFull = 256;          // groups per task in a full scan
+constexpr int kChunkFull = 256;          // groups per task in a full scan, where staging the
+constexpr int kChunkFullSmall = 64;      //   rows takes long or not
+constexpr size_t kSmallRows = 40 * 1024;
 constexpr int kSplitGrid = 2048;         // workgroups of a split launch
 
 // Exclusive prefix sums over the workgroup of three per-thread counts; also
@@ -512,15 +514,63 @@ map_columns(int32_t* __restrict__ idx, size_t n, const int32_t* __restrict__ map
     if (i < n && idx[i] >= 0) idx[i] = map[idx[i]];
 }
 
-template <typename T>
-int alloc_async(T** p, size_t count, hipStream_t s) {
-    *p = nullptr;
-    hipError_t e = hipMallocAsync(reinterpret_cast<void**>(p), std::max<size_t>(count, 1) * sizeof(T), s);
-    if (e != hipSuccess) {
-        *p = nullptr;
-        tmlib::set_error("hipMallocAsync(%zu bytes) failed: %s", count * sizeof(T), hipGetErrorString(e));
-        return TM_ENOMEM;
+// Scratch of a split launch: its plan and the partial lists.
+struct SplitScratch {
+    int4 *tasks, *merges;
+    int32_t *meta, *pt, *ps;
+    float* pq;
+    int slots;
+    SplitScratch(tmlib::Scratch& m, int32_t B, int32_t N, int64_t most_tasks)
+        : slots(static_cast<int>(std::min<int64_t>(kSlotBudget, most_tasks))) {
+        const size_t lists = static_cast<size_t>(slots) * N;
+        m.add(tasks, static_cast<size_t>(B) + slots);
+        m.add(merges, B);
+        m.add(meta, 4);
+        m.add(pt, lists);
+        m.add(ps, lists);
+        m.add(pq, lists);
     }
+};
+
+size_t staged_bytes(const tm_library* lib) {
+    return static_cast<size_t>(std::max(lib->band_rows, 1)) * lib->row_width * sizeof(float);
+}
+int chunk_full(const tm_library* lib) {
+    return lib->n_bands == 1 && staged_bytes(lib) <= kSmallRows ? kChunkFullSmall : kChunkFull;
+}
+
+// Most tasks of a split launch over B patterns of up to n_items items.
+int64_t most_tasks(int32_t B, int32_t n_items, int chunk) {
+    return static_cast<int64_t>(B) * (1 + (n_items + chunk - 1) / chunk);
+}
+
+// One split launch over the patterns with (full[b] != 0) == want_full:
+// candidate lists (cand, cnt) of up to n_items ids, or all n_items groups.
+int split_pass(const tm_library* lib, const float* polar, const double* norms, int32_t B, int32_t N,
+               const int32_t* full, bool want_full, const int32_t* cand, const int32_t* cnt,
+               int32_t n_items, const SplitScratch& sc, int32_t* top_template, int32_t* top_angle,
+               float* top_score, bool compact, hipStream_t s) {
+    // workgroups for the tasks, as many as the chip holds (their LDS: the
+    // band's rows)
+    const int chunk = want_full ? chunk_full(lib) : kChunkCand;
+    const size_t lds = staged_bytes(lib);
+    const int64_t fit = 256 * std::min<int64_t>(8, std::max<int64_t>(1, static_cast<int64_t>(160 * 1024 / lds)));
+    const int grid = static_cast<int>(std::max<int64_t>(1, std::min({most_tasks(B, n_items, chunk), fit,
+                                                                     static_cast<int64_t>(kSplitGrid)})));
+    const tmlib::SplitWork work{sc.tasks, sc.meta, sc.pt, sc.ps, sc.pq, grid};
+    hipLaunchKernelGGL(plan_split, dim3(1), dim3(kPlanThreads), 0, s, full, want_full ? 1 : 0, cnt,
+                       n_items, B, chunk, sc.slots, sc.tasks, sc.merges, sc.meta);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return tmlib::hip_fail(e, "plan_split launch");
+    if (int r = tmlib::launch_match(lib, polar, norms, B, N, top_template, top_angle, top_score,
+                                    nullptr, nullptr, cand, cand ? n_items : 0, nullptr, nullptr,
+                                    compact, s, &work))
+        return r;
+    const int mgrid = std::max(1, std::min((B + 3) / 4, 256));
+    hipLaunchKernelGGL(merge_split, dim3(mgrid), dim3(256), 0, s, sc.merges, sc.meta, norms, N, sc.pt,
+                       sc.ps, sc.pq, top_template, top_angle, top_score);
+    e = hipGetLastError();
+    if (e != hipSuccess) return tmlib::hip_fail(e, "merge_split launch");
     return TM_OK;
 }
 
@@ -534,24 +584,27 @@ int tmlib::certified_rescore(const tm_library* lib, const float* polar, const do
                              const int32_t* first_col, int32_t n_list) {
     const int Tp = lib->Tp;
     n_first = std::max(N, std::min(n_first, std::min(tmlib::kMaxN, Tp)));
-    int r = TM_OK;
-    int32_t *t0 = nullptr, *s0 = nullptr, *t1 = nullptr, *s1 = nullptr;
-    float *q0 = nullptr, *q1 = nullptr;
-    int32_t *cand = nullptr, *cnt = nullptr, *full = nullptr;
+    int32_t *t0, *s0 = nullptr, *t1, *s1, *cand, *cnt, *full;
+    float *q0 = nullptr, *q1;
     const size_t bn = static_cast<size_t>(B) * N;
     const size_t bf = static_cast<size_t>(B) * n_first;
-    if (!r) r = alloc_async(&t0, bf, s);
-    if (!r && !first_q) r = alloc_async(&s0, bf, s);   // the top-n's angles and scores
-    if (!r && !first_q) r = alloc_async(&q0, bf, s);
-    if (!r) r = alloc_async(&t1, bn, s);
-    if (!r) r = alloc_async(&s1, bn, s);
-    if (!r) r = alloc_async(&q1, bn, s);
-    if (!r) r = alloc_async(&cand, static_cast<size_t>(B) * cap, s);
-    if (!r) r = alloc_async(&cnt, B, s);
-    if (!r) r = alloc_async(&full, B, s);
+    tmlib::Scratch mem;
+    mem.add(t0, bf);
+    if (!first_q) {                              // the top-n's angles and scores
+        mem.add(s0, bf);
+        mem.add(q0, bf);
+    }
+    mem.add(t1, bn);
+    mem.add(s1, bn);
+    mem.add(q1, bn);
+    mem.add(cand, static_cast<size_t>(B) * cap);
+    mem.add(cnt, B);
+    mem.add(full, B);
+    SplitScratch sc(mem, B, N, std::max(most_tasks(B, cap, kChunkCand), most_tasks(B, lib->n_groups, chunk_full(lib))));
+    int r = mem.allocate(s);
     // 1. the n_first best estimates (or of the caller's short list), scored
     // exactly: their N-th best, q_N
-    if (first_q) {
+    if (!r && first_q) {
         if (n_list < n_first) {
             tmlib::set_error("first-pass list of %d entries for %d picks", n_list, n_first);
             r = TM_EINVAL;
@@ -597,34 +650,10 @@ int tmlib::certified_rescore(const tm_library* lib, const float* polar, const do
     // 3. exact scores of the candidates; full scans where the set was too
     // large. Both passes are split launches: long candidate lists and full
     // scans are spread over many workgroups.
-    int4 *tasks = nullptr, *merges = nullptr;
-    int32_t *meta = nullptr, *pt = nullptr, *ps = nullptr;
-    float* pq = nullptr;
-    const int slots = kSlotBudget;
-    if (!r) r = alloc_async(&tasks, static_cast<size_t>(B) + slots, s);
-    if (!r) r = alloc_async(&merges, B, s);
-    if (!r) r = alloc_async(&meta, 4, s);
-    if (!r) r = alloc_async(&pt, static_cast<size_t>(slots) * N, s);
-    if (!r) r = alloc_async(&ps, static_cast<size_t>(slots) * N, s);
-    if (!r) r = alloc_async(&pq, static_cast<size_t>(slots) * N, s);
-    const int grid = static_cast<int>(std::min<int64_t>(static_cast<int64_t>(B) + slots, kSplitGrid));
-    const tmlib::SplitWork work{tasks, meta, pt, ps, pq, grid};
     auto pass = [&](bool want_full) -> int {
-        hipLaunchKernelGGL(plan_split, dim3(1), dim3(kPlanThreads), 0, s, full, want_full ? 1 : 0,
-                           want_full ? nullptr : cnt, want_full ? lib->n_groups : cap, B,
-                           want_full ? kChunkFull : kChunkCand, slots, tasks, merges, meta);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return tmlib::hip_fail(e, "plan_split launch");
-        if (int rr = tmlib::launch_match(lib, polar, norms, B, N, top_template, top_angle, top_score,
-                                         nullptr, nullptr, want_full ? nullptr : cand,
-                                         want_full ? 0 : cap, nullptr, nullptr, compact, s, &work))
-            return rr;
-        const int mgrid = std::max(1, std::min((B + 3) / 4, 256));
-        hipLaunchKernelGGL(merge_split, dim3(mgrid), dim3(256), 0, s, merges, meta, norms, N, pt, ps,
-                           pq, top_template, top_angle, top_score);
-        e = hipGetLastError();
-        if (e != hipSuccess) return tmlib::hip_fail(e, "merge_split launch");
-        return TM_OK;
+        return split_pass(lib, polar, norms, B, N, full, want_full, want_full ? nullptr : cand,
+                          want_full ? nullptr : cnt, want_full ? lib->n_groups : cap, sc, top_template,
+                          top_angle, top_score, compact, s);
     };
     if (!r) r = pass(false);
     if (!r) {
@@ -634,11 +663,17 @@ int tmlib::certified_rescore(const tm_library* lib, const float* polar, const do
         if (e != hipSuccess) r = tmlib::hip_fail(e, "merge_first launch");
     }
     if (!r) r = pass(true);
-    for (void* p : {static_cast<void*>(t0), static_cast<void*>(s0), static_cast<void*>(q0),
-                    static_cast<void*>(t1), static_cast<void*>(s1), static_cast<void*>(q1),
-                    static_cast<void*>(cand), static_cast<void*>(cnt), static_cast<void*>(full),
-                    static_cast<void*>(tasks), static_cast<void*>(merges), static_cast<void*>(meta),
-                    static_cast<void*>(pt), static_cast<void*>(ps), static_cast<void*>(pq)})
-        if (p) (void)hipFreeAsync(p, s);
-    return r;
+    return mem.release(s, r);
+}
+
+int tmlib::full_scans(const tm_library* lib, const float* polar, const double* norms, int32_t B,
+                      int32_t N, const int32_t* full, int32_t* top_template, int32_t* top_angle,
+                      float* top_score, bool compact, hipStream_t s) {
+    tmlib::Scratch mem;
+    SplitScratch sc(mem, B, N, most_tasks(B, lib->n_groups, chunk_full(lib)));
+    int r = mem.allocate(s);
+    if (!r)
+        r = split_pass(lib, polar, norms, B, N, full, true, nullptr, nullptr, lib->n_groups, sc,
+                       top_template, top_angle, top_score, compact, s);
+    return mem.release(s, r);
 }

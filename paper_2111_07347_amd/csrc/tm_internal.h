@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdarg>
 #include <cstdint>
 #include <string>
@@ -27,6 +28,31 @@ int hip_fail(hipError_t e, const char* what);
         hipError_t e_ = (call);                        \
         if (e_ != hipSuccess) return tmlib::hip_fail(e_, #call); \
     } while (0)
+
+// Scratch of a call: the arrays it needs, laid out one after the other in one
+// stream-ordered allocation (each allocation costs the host some
+// microseconds, as much as a small kernel runs).
+class Scratch {
+public:
+    // p will point to n elements (at least one) once allocated.
+    template <typename T>
+    void add(T*& p, size_t n) {
+        p = nullptr;
+        slots_.push_back({&p, bytes_});
+        bytes_ += (std::max<size_t>(n, 1) * sizeof(T) + 255) / 256 * 256;
+    }
+    // TM_ENOMEM with a message when there is no such memory.
+    int allocate(hipStream_t s);
+    // Gives the memory back behind the work on s; r if it is an error, else
+    // the status of this call.
+    int release(hipStream_t s, int r);
+
+private:
+    struct Slot { void* p; size_t at; };
+    std::vector<Slot> slots_;
+    size_t bytes_ = 0;
+    char* base_ = nullptr;
+};
 
 // Shared validation of a tm_polar_grid (TM_OK or TM_EINVAL with a message).
 int validate_grid(const tm_polar_grid* g);
@@ -128,6 +154,12 @@ int certified_rescore(const tm_library* lib, const float* polar, const double* n
                       hipStream_t s, const float* first_q = nullptr,
                       const int32_t* first_col = nullptr, int32_t n_list = 0);
 
+// Plain scans of the patterns with full[b] != 0 into their output rows, each
+// spread over many workgroups (tm_certify.hip). Enqueued on s.
+int full_scans(const tm_library* lib, const float* polar, const double* norms, int32_t B,
+               int32_t N, const int32_t* full, int32_t* top_template, int32_t* top_angle,
+               float* top_score, bool compact, hipStream_t s);
+
 // Window upper bounds (tm_bound.hip): library data built at load (only when
 // every template weight is non-negative and the window image fits the LDS
 // budget), its release, the bounds of a batch, and the exact search built
@@ -138,15 +170,50 @@ void bound_release(tm_library* L);
 // Bounds in chunk-slot order (Qc [B, bnd_chunks * 64], -inf for empty
 // slots; d_bnd_tid maps slots to templates) or, with template_order, in
 // template order (Qt [B, T']).
-// lane_q, lane_c (optional, device, B x 1024): each lane's largest bound
-// and its chunk-slot column (-inf / -1 for none), in rows of *n_list
-// entries (the workgroup's lanes).
+// split: workgroups per pattern. lane_q, lane_c (optional, device): each
+// lane's largest bound and its chunk-slot column (-inf / -1 for none), a row
+// per pattern with the lanes of its workgroups. amax (optional, device [B]):
+// the largest |P| over the touched rows (0 for a non-finite norm).
 int bound_scores_impl(const tm_library* L, const float* polar, const double* norms, int32_t B,
                       float* out, bool template_order, bool compact, hipStream_t s,
-                      float* lane_q = nullptr, int32_t* lane_c = nullptr, int* n_list = nullptr);
+                      float* lane_q = nullptr, int32_t* lane_c = nullptr, int split = 1,
+                      float* amax = nullptr);
 int bound_match(const tm_library* lib, const float* polar, const double* norms, int32_t B,
                 int32_t N, double cap_frac, int32_t* n_rescored, int32_t* top_template,
                 int32_t* top_angle, float* top_score, bool compact, hipStream_t s);
+
+// The rest of the window-bound search (tm_search.hip): library data built at
+// load for libraries with window bounds (recs / seg: the per-template
+// records of the match kernel, host; rows: the touched rows), its release,
+// and the exact top-N of a batch from each pattern's largest |P| over the
+// touched rows (amax [B]), bounds Qc [B, n_cs] in chunk-slot order and each
+// pattern's n_list large bounds (lane_q, their columns lane_c,
+// -1 for none). Enqueued on s.
+int search_prepare(tm_library* L, const std::vector<uint32_t>& recs,
+                   const std::vector<int32_t>& seg, const std::vector<int32_t>& rows,
+                   const std::vector<int32_t>& band_off, hipStream_t s, size_t& bytes);
+void search_release(tm_library* L);
+int refine_search(const tm_library* lib, const float* polar, const double* norms, int32_t B,
+                  int32_t N, const float* amax, const float* Qc, int32_t n_cs,
+                  const float* lane_q, const int32_t* lane_c, int32_t n_list, int32_t* top_template,
+                  int32_t* top_angle, float* top_score, bool compact, hipStream_t s);
+
+// The same for sparse libraries (sr_all), which need no bounds from outside,
+// and for listed templates (items [B, n_items], ascending, none twice).
+int search_all(const tm_library* lib, const float* polar, const double* norms, int32_t B,
+               int32_t N, int32_t* top_template, int32_t* top_angle, float* top_score,
+               bool compact, hipStream_t s);
+bool search_items_pays(const tm_library* lib, int32_t n_items);
+int search_items(const tm_library* lib, const float* polar, const double* norms, int32_t B,
+                 int32_t N, const int32_t* items, int32_t n_items, int32_t* top_template,
+                 int32_t* top_angle, float* top_score, bool compact, hipStream_t s);
+
+// The plain path's top-N by search: whether that pays for B patterns, and
+// the search (without scratch to be had: the plain scan). Enqueued on s.
+bool search_pays(const tm_library* lib, int32_t B);
+int search_top(const tm_library* lib, const float* polar, const double* norms, int32_t B, int32_t N,
+               int32_t* top_template, int32_t* top_angle, float* top_score, bool compact,
+               hipStream_t s);
 
 constexpr int kMaxN = TM_MAX_N;
 constexpr int kWave = 64;
@@ -235,7 +302,24 @@ struct tm_library {
     int32_t* d_bnd_tid = nullptr;     // [bnd_chunks * 64]: template of each chunk slot, -1 none
     std::vector<int32_t> bnd_tid;     // host copy
     float* d_bnd_cfac = nullptr;      // [bnd_chunks * 64]: margin factor, -1 for no template
-    int32_t* d_bnd_part = nullptr;    // [9 + 17]: chunk ranges of 8 and of 16 waves
+    int32_t* d_bnd_part = nullptr;    // [1025]: chunk ranges of about equal units
+
+    // search by refinement of bounds (tm_search.hip)
+    bool search = false;
+    bool sr_all = false;              // sparse: the search kernel bounds all templates itself
+    uint32_t* d_sr_recs = nullptr;    // window records: image entry | float16 weight << 16,
+                                      // per template and sector in units of 4
+    uint32_t* d_sr_head = nullptr;    // per column 16 bytes: first unit, margin factor x 2^10
+                                      // (float32), units per sector (8 bits each)
+    uint32_t* d_sr_xrecs = nullptr;   // exact records in the match kernel's order: global row
+                                      // << 20 | touched row << 10 | column, float32 weight
+    int32_t* d_sr_xhead = nullptr;    // [Tp][2] first exact record, number (padded to batches)
+    int32_t* d_sr_tid = nullptr;      // template of each column, -1 none (the bounds' columns,
+                                      // or an order of its own with sr_all)
+    int32_t* d_sr_col = nullptr;      // [Tp] column of each template
+    uint32_t* d_sr_drecs = nullptr;   // sr_all: window records by step and lane
+    uint32_t* d_sr_chunk = nullptr;   // sr_all: per 64 columns 16 bytes: first step, (unused),
+                                      // steps per sector (8 bits each)
 
     // host copies used for validation and info
     std::vector<double> tnorm;      // [Tp]

@@ -175,6 +175,7 @@ void release(tm_library* L) {
     (void)hipFree(L->d_prof_max);
     tmlib::fft_release(L);
     tmlib::bound_release(L);
+    tmlib::search_release(L);
     delete L;
 }
 
@@ -432,6 +433,7 @@ extern "C" int tm_load_library(const double* kx, const double* ky, const double*
     if (!r) r = upload(&L->d_prof_max, prof_max, s, bytes);
     if (!r && (flags & TM_LIB_FFT)) r = tmlib::fft_prepare(L, pix, s, bytes);
     if (!r) r = tmlib::bound_prepare(L, pix, row_index, s, bytes);
+    if (!r) r = tmlib::search_prepare(L, G != 1 ? recs1 : recs, G != 1 ? seg1 : seg, rows, band_off, s, bytes);
     if (!r) {
         hipError_t e = hipStreamSynchronize(s);
         if (e != hipSuccess) r = tmlib::hip_fail(e, "hipStreamSynchronize");

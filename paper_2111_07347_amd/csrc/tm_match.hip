@@ -577,10 +577,20 @@ int tmlib::match_batch_impl(const tm_library* lib, const float* polar, const dou
     if (coarse == TM_COARSE_BOUND)
         return tmlib::bound_match(lib, polar, norms, B, N, rescore_keep, n_rescored, top_template,
                                   top_angle, top_score, compact, s);
+    // Scratch may be taken here (not in the allocation-free entry, nor while
+    // the stream is captured: the plain scan needs none)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (!scratch && s) TM_HIP(hipStreamIsCapturing(s, &capture));
+    const bool may_allocate = !scratch && capture == hipStreamCaptureStatusNone;
     if (n_keep == 0) {
-        int r = tmlib::launch_match(lib, polar, norms, B, N, top_template, top_angle, top_score,
-                                    best_score, best_angle, nullptr, 0, nullptr, nullptr, compact,
-                                    s);
+        // Without per-template outputs only the N best matter: the same rows
+        // come from the search with bounds (tm_bound.hip, tm_search.hip)
+        int r = !best_score && may_allocate && tmlib::search_pays(lib, B)
+                    ? tmlib::search_top(lib, polar, norms, B, N, top_template, top_angle, top_score,
+                                        compact, s)
+                    : tmlib::launch_match(lib, polar, norms, B, N, top_template, top_angle, top_score,
+                                          best_score, best_angle, nullptr, 0, nullptr, nullptr, compact,
+                                          s);
         if (!r && n_rescored) r = tmlib::fill_i32(n_rescored, B, lib->Tp, s);
         return r;
     }
@@ -596,9 +606,13 @@ int tmlib::match_batch_impl(const tm_library* lib, const float* polar, const dou
                               static_cast<size_t>(B) * n_items * sizeof(int32_t), s));
     }
     int r = tmlib::prefilter_kept(lib, profiles, B, n_keep, prec, items, n_items, mirror, s, S);
-    if (!r) r = tmlib::launch_match(lib, polar, norms, B, N, top_template, top_angle, top_score,
-                                    nullptr, nullptr, items, n_items, nullptr, nullptr, compact,
-                                    s);
+    // of the kept templates, too, only the N best matter
+    const bool search = may_allocate && tmlib::search_items_pays(lib, n_items);
+    if (!r)
+        r = search ? tmlib::search_items(lib, polar, norms, B, N, items, n_items, top_template, top_angle,
+                                         top_score, compact, s)
+                   : tmlib::launch_match(lib, polar, norms, B, N, top_template, top_angle, top_score,
+                                         nullptr, nullptr, items, n_items, nullptr, nullptr, compact, s);
     if (!r && n_rescored) r = tmlib::fill_i32(n_rescored, B, n_items, s);
     if (!scratch) {
         hipError_t e = hipFreeAsync(items, s);

@@ -1,5 +1,6 @@
 // Error reporting, device presence and version for libtm.
 #include <cstdio>
+#include <cstring>
 #include <mutex>
 
 #include "tm_internal.h"
@@ -22,6 +23,27 @@ void clear_error() { g_error.clear(); }
 int hip_fail(hipError_t e, const char* what) {
     set_error("%s failed: %s (%d)", what, hipGetErrorString(e), static_cast<int>(e));
     return TM_EHIP;
+}
+
+int Scratch::allocate(hipStream_t s) {
+    hipError_t e = hipMallocAsync(reinterpret_cast<void**>(&base_), std::max<size_t>(bytes_, 256), s);
+    if (e != hipSuccess) {
+        base_ = nullptr;
+        set_error("hipMallocAsync(%zu bytes) failed: %s", bytes_, hipGetErrorString(e));
+        return TM_ENOMEM;
+    }
+    for (const Slot& v : slots_) {
+        void* p = base_ + v.at;
+        std::memcpy(v.p, &p, sizeof(p));
+    }
+    return TM_OK;
+}
+
+int Scratch::release(hipStream_t s, int r) {
+    if (!base_) return r;
+    hipError_t e = hipFreeAsync(base_, s);
+    base_ = nullptr;
+    return r ? r : e != hipSuccess ? hip_fail(e, "hipFreeAsync") : TM_OK;
 }
 
 int require_device() {
