@@ -598,8 +598,10 @@ typedef struct {
  *   opts         host, read during the call.
  *   out          device, [B, H, W] float32, written (may not alias patterns).
  *   centre_out   device, [B, 2] float64 (cx, cy), written, or NULL.
- * Scratch (two float32 images per pattern of a chunk, at most 1 GiB) comes
- * from the stream-ordered allocator.
+ * A non-finite pixel reaches the outputs within the radius of G(sigma_blur)
+ * and G(sigma_min), or G(sigma_max), together; the others do not depend on it.
+ * Scratch (two float64 per pattern, when centre_out is NULL) comes from the
+ * stream-ordered allocator.
  * Errors: TM_EINVAL, TM_ENOMEM, TM_EHIP, TM_ENODEV. */
 int tm_preprocess(const void* patterns, tm_dtype dtype, int32_t B, int32_t H, int32_t W,
                   const tm_preprocess_opts* opts, float* out, double* centre_out,

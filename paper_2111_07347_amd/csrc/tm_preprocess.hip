@@ -7,25 +7,37 @@
 //                  |x - W/2| <= r_box, |y - H/2| <= r_box, then the
 //                  intensity-weighted centroid (float64) of the box pixels
 //                  >= frac times that maximum.
-//   row_kernel     one wave per image row (4 per workgroup): the row of the
-//                  centred pattern, out(x, y) = in(x + cx - W/2, y + cy - H/2)
-//                  (bilinear, zero outside), or of an intermediate image, is
-//                  built in LDS, then correlated along x with one or two
-//                  sampled Gaussians (mirror boundary).
-//   col_tile_kernel  32-column strips of images up to 256 rows, staged whole
-//                  in LDS: correlation along y with one or two Gaussians; two
-//                  give the difference of Gaussians; an optional threshold
-//                  sets values below it to 0. col_kernel does the same for
-//                  taller images, one thread per column (coalesced rows).
+//   filter_kernel  everything else in one pass over the pattern.
 //
 // Gaussians: exp(-t^2 / (2 sigma^2)) on |t| <= floor(4 sigma + 0.5),
 // normalised in float64 on the host, applied in float32; mirror boundary
-// (... c b a | a b c ...) by folding indices modulo 2n. The passes run over
-// chunks of patterns so that the two float32 scratch images stay within
-// 1 GiB. The filters cost 2 (2 r + 1) FMAs per pixel and Gaussian, more
-// than the machine balance for the default radii, but each pass also
-// streams images through HBM (about ten image sizes per pattern with all
-// steps on) and waits on its staging loads.
+// (... c b a | a b c ...) by folding indices modulo 2n. A symmetric filter
+// keeps that extension, so the blur of a difference of Gaussians is the
+// difference of two separable filters, K1 = G(blur) G(min) and K2 = G(blur)
+// G(max), whose taps are convolved in float64 on the host: one pass along x
+// and one along y in all.
+//
+// filter_kernel: a workgroup of 4 waves owns 32 columns of a pattern and goes
+// down its rows in blocks of 32. Per block the centred rows, out(x, y) = in(x +
+// cx - W/2, y + cy - H/2) (bilinear, zero outside), are staged in LDS with
+// mirrored halos; the correlations along x and y are products with banded
+// Toeplitz matrices on the matrix cores (v_mfma_f32_16x16x4_f32: float32 in and
+// out), one 16 x 16 tile per wave. Rows filtered along x wait in a ring until
+// the reach of the filters along y is there. The Toeplitz operands are read
+// from a zero-padded tap table in LDS (entry k - n), and rows outside the
+// image are ring rows at the mirrored index. A 16-column tile of a filter of
+// radius r takes 16 + 2 r products per output, against 2 r + 1 of the filter
+// alone; the vector units' share is the staging.
+// Measured (1024 uint16 patterns of 256 x 256, sigma 1 / 6 / 1, all steps):
+// 478 us, 60 % of it matrix-core issue, against 1061 us of separate row and
+// column passes for the difference and the blur on the vector units (ten image
+// sizes of HBM traffic). Strips of 64 columns and 8 waves take 453 us, but
+// their rings exceed the LDS at the largest reach.
+//
+// A zero tap still multiplies in a matrix product: non-finite pixels are
+// staged as 0 and kept as bits of the columns that their reach along x covers;
+// outputs that such a row reaches along y become infinite or NaN as the sum of
+// positive taps times these pixels is, and the difference of two such sums.
 #include <algorithm>
 #include <cmath>
 
@@ -34,58 +46,19 @@
 namespace {
 
 constexpr int kMaxRadius = 64;            // sigma <= 15.9
-constexpr int kRowThreads = 256;
-constexpr int kRowWaves = kRowThreads / 64;
-constexpr size_t kLdsLimit = 156 * 1024;
-constexpr int kTileRows = 256;            // column-strip kernel: images up to this high
-constexpr int kTapBlock = 8;              // taps per weight block of the column-strip kernel
-constexpr int kStageBatch = 8;            // loads in flight per thread while staging
-constexpr int kRowBatch = 4;              // columns per lane in flight while staging a row
-
-// Floats of one wave's row strip: the row rounded up to 256 columns (the
-// last chunk's lanes read past W) plus the two halos of rh (a multiple of 4)
-// and 16 more, which the last tap block's window may reach.
-__host__ __device__ inline int row_strip(int W, int rh) { return (W + 255) / 256 * 256 + 2 * rh + 16; }
-
+constexpr int kMaxReach = 2 * kMaxRadius; // of a filter and the blur
+constexpr int kThreads = 256;             // 4 waves: 2 x 2 tiles of 16 x 16
+constexpr int kTile = 32;                 // columns of a strip, rows of a block
 constexpr int kCentreThreads = 256;
-constexpr size_t kScratchBudget = size_t(1) << 30;
+constexpr int kXcds = 8;
+constexpr int kMaxGrid = 1 << 22;         // workgroups of a launch
 
-// Zero-padded copy of a tap table for the row kernel: wp[t + r4] = w(t) for
-// t in [-r4, r4 + 7], r4 = the radius rounded up to a multiple of 4, zero
-// past the radius.
-constexpr int kWLen = 2 * kMaxRadius + 16;
-
-struct Taps {
-    int r;
-    float w[2 * kMaxRadius + 1];
-    alignas(32) float wp[kWLen];
+// A symmetric filter: its reach, that rounded up to a multiple of 4 (0 taps
+// past the reach) and w[t], 0 <= t <= r.
+struct Filter {
+    int reach, r;
+    float w[kMaxReach + 1];
 };
-
-
-// acc[m] += sum_t w(t) * row[c + m + t], m < 4, over the padded table of
-// tp, in blocks of 8 taps: per block one 32-byte scalar load of weights and
-// a 12-float window (aligned 16-byte LDS reads) feed 32 FMAs. c and the
-// block starts are multiples of 4.
-__device__ __forceinline__ void conv4(const float* row, int c, const Taps& tp, float (&acc)[4]) {
-    const int r4 = (tp.r + 3) & ~3;
-    for (int t0 = -r4; t0 <= r4; t0 += 8) {
-        float w[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) w[j] = tp.wp[t0 + r4 + j];
-        const float4* p = static_cast<const float4*>(__builtin_assume_aligned(row + c + t0, 16));
-        float win[12];
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const float4 v = p[q];
-            win[4 * q] = v.x; win[4 * q + 1] = v.y; win[4 * q + 2] = v.z; win[4 * q + 3] = v.w;
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-#pragma unroll
-            for (int m = 0; m < 4; ++m) acc[m] += w[j] * win[m + j];
-    }
-}
-
 
 __device__ __forceinline__ int mirror(int i, int n) {
     if (static_cast<unsigned>(i) < static_cast<unsigned>(n)) return i;
@@ -96,12 +69,6 @@ __device__ __forceinline__ int mirror(int i, int n) {
     int j = i % p;
     if (j < 0) j += p;
     return j < n ? j : p - 1 - j;
-}
-
-template <typename Tin>
-__device__ __forceinline__ float load_px(const Tin* img, int H, int W, int y, int x) {
-    return (x >= 0 && x < W && y >= 0 && y < H) ? static_cast<float>(img[static_cast<size_t>(y) * W + x])
-                                                 : 0.0f;
 }
 
 template <typename Tin>
@@ -162,323 +129,314 @@ centre_kernel(const Tin* __restrict__ patterns, int H, int W, int r_box, double 
     }
 }
 
-// One image row per wave (4 rows per workgroup): the row of the source is
-// staged in the wave's LDS strip with a mirrored halo of rh columns on each
-// side (rh a multiple of 4, at least the largest radius), then correlated
-// along x with taps a (-> out_a) and, when out_b is given, taps b
-// (-> out_b). The source is the input pattern (`in`), centred when `centre`
-// is given, else the float image `src`. Lanes own 4 consecutive columns of
-// each 256-column chunk and share one tap window among them (conv4).
-template <typename Tin>
-__global__ void __launch_bounds__(kRowThreads)
-row_kernel(const Tin* __restrict__ in, const float* __restrict__ src,
-           const double* __restrict__ centre, int H, int W, Taps a, Taps bt, int rh,
-           float* __restrict__ out_a, float* __restrict__ out_b) {
-    extern __shared__ float lds[];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int y = blockIdx.x * kRowWaves + wave, b = blockIdx.y;
-    if (y >= H) return;    // the wave leaves; no workgroup barrier follows
-    const int span = W + 2 * rh;
-    float* row = lds + static_cast<size_t>(wave) * row_strip(W, rh);
-    const size_t base = (static_cast<size_t>(b) * H + y) * W;
-    if (in && centre) {
-        const Tin* img = in + static_cast<size_t>(b) * H * W;
-        const double dx = centre[2 * b] - 0.5 * W, dy = centre[2 * b + 1] - 0.5 * H;
-        const double ys = y + dy;
-        const double yf = floor(ys);
-        const float fy = static_cast<float>(ys - yf);
-        const int yi = static_cast<int>(fmax(fmin(yf, 1e9), -1e9));
-        // kRowBatch columns per lane in flight: all taps are loaded first
-        for (int i0 = lane; i0 < span; i0 += 64 * kRowBatch) {
-            float p[kRowBatch][4], fx[kRowBatch];
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Zero-padded taps of a filter for the Toeplitz operands: entry 15 + d holds
+// tap d - r (0 <= d <= 2 r), zeros 15 deep on either side.
+__host__ __device__ constexpr int table_len(int r) { return 2 * r + 1 + 30; }
+
+// Rows of the ring: a block's filters along y run when the blocks that hold
+// their reach are there, and still find the rows before the block.
+__host__ __device__ constexpr int blocks_ahead(int r) { return (r + kTile - 1) / kTile; }
+__host__ __device__ constexpr int ring_rows(int r) {
+    return (kTile * (blocks_ahead(r) + 1) + r + kTile - 1) / kTile * kTile;
+}
+
+// Product of a 16 x (16 + 2 r) and a (16 + 2 r) x 16 operand (4 | r, an even
+// number of steps of 4), one of them banded: from both ends of k toward the
+// middle in two sums, so that the small taps are added first (less rounding)
+// and two products are in flight. a(k) and b(k) point to a lane's element at
+// k; SA and SB floats further (back) lies that of the next (last) step, which
+// holds for b as far as `whole` says: whole(k, d) for the 4 steps from k in
+// direction d.
+template <int SA, int SB, typename FA, typename FB, typename FW>
+__device__ __forceinline__ f32x4 banded(int r, FA a, FB b, FW whole) {
+    f32x4 lo = {0.0f, 0.0f, 0.0f, 0.0f}, hi = lo;
+    const int pairs = 2 + r / 4, e = 12 + 2 * r;
+    int p = 0;
+#pragma unroll 1
+    for (; p + 4 <= pairs; p += 4) {
+        const int k = 4 * p, l = e - 4 * p;
+        if (!whole(k, 1) || !whole(l, -1)) break;
+        const float *al = a(k), *bl = b(k), *ah = a(l), *bh = b(l);
 #pragma unroll
-            for (int u = 0; u < kRowBatch; ++u) {
-                const int i = min(i0 + 64 * u, span - 1);
-                const double xs = mirror(i - rh, W) + dx;
-                const double xf = floor(xs);
-                fx[u] = static_cast<float>(xs - xf);
-                const int xi = static_cast<int>(fmax(fmin(xf, 1e9), -1e9));
-                p[u][0] = load_px(img, H, W, yi, xi);
-                p[u][1] = load_px(img, H, W, yi, xi + 1);
-                p[u][2] = load_px(img, H, W, yi + 1, xi);
-                p[u][3] = load_px(img, H, W, yi + 1, xi + 1);
-            }
-#pragma unroll
-            for (int u = 0; u < kRowBatch; ++u) {
-                const int i = i0 + 64 * u;
-                if (i < span)
-                    row[i] = (1.0f - fx[u]) * (1.0f - fy) * p[u][0] + fx[u] * (1.0f - fy) * p[u][1] +
-                             (1.0f - fx[u]) * fy * p[u][2] + fx[u] * fy * p[u][3];
-            }
-        }
-    } else {
-        for (int i0 = lane; i0 < span; i0 += 64 * kRowBatch) {
-            float v[kRowBatch];
-#pragma unroll
-            for (int u = 0; u < kRowBatch; ++u) {
-                const size_t q = base + mirror(min(i0 + 64 * u, span - 1) - rh, W);
-                v[u] = in ? static_cast<float>(in[q]) : src[q];
-            }
-#pragma unroll
-            for (int u = 0; u < kRowBatch; ++u)
-                if (i0 + 64 * u < span) row[i0 + 64 * u] = v[u];
+        for (int u = 0; u < 4; ++u) {
+            lo = __builtin_amdgcn_mfma_f32_16x16x4f32(al[SA * u], bl[SB * u], lo, 0, 0, 0);
+            hi = __builtin_amdgcn_mfma_f32_16x16x4f32(ah[-SA * u], bh[-SB * u], hi, 0, 0, 0);
         }
     }
-    // the tail of the strip (past the right halo) holds zeros: the zero
-    // weights of the last tap blocks read it
-    for (int i = span + lane; i < row_strip(W, rh); i += 64) row[i] = 0.0f;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    // each lane owns 4 consecutive columns of every 256-column chunk
-    for (int x0 = 0; x0 < W; x0 += 4 * 64) {
-        const int x = x0 + 4 * lane;
-        float va[4] = {0.0f, 0.0f, 0.0f, 0.0f}, vb[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        conv4(row, x + rh, a, va);
-        if (out_b) conv4(row, x + rh, bt, vb);
-        if ((W & 3) == 0 && x + 3 < W) {
-            *reinterpret_cast<float4*>(out_a + base + x) = make_float4(va[0], va[1], va[2], va[3]);
-            if (out_b) *reinterpret_cast<float4*>(out_b + base + x) = make_float4(vb[0], vb[1], vb[2], vb[3]);
-        } else {
+#pragma unroll 1
+    for (; p < pairs; ++p) {
+        lo = __builtin_amdgcn_mfma_f32_16x16x4f32(*a(4 * p), *b(4 * p), lo, 0, 0, 0);
+        hi = __builtin_amdgcn_mfma_f32_16x16x4f32(*a(e - 4 * p), *b(e - 4 * p), hi, 0, 0, 0);
+    }
+    return lo + hi;
+}
+
+// Place of column n of a ring row: in odd rows the halves change places, so
+// that the 2 rows that half a wave reads do not meet in an LDS bank.
+__device__ __forceinline__ int ring_at(int row, int n) {
+    return row * kTile + (n ^ ((row & 1) << 4));
+}
+
+// Floats of a staged row: rows 2 (mod 4) apart put the 16 x 2 elements that
+// half a wave reads in different banks.
+__host__ __device__ constexpr int staged_pitch(int R) { return (kTile + 2 * R) / 4 * 4 + 2; }
+
+// TWO: out = K1 - K2, else K1 alone. Dynamic LDS: staged block, rings, tables,
+// bits of non-finite pixels.
+template <typename Tin, bool TWO>
+__global__ void __launch_bounds__(kThreads, 4)
+filter_kernel(const Tin* __restrict__ in, const double* __restrict__ centre, int B, int H, int W,
+              int strips, Filter f1, Filter f2, bool thresh, float threshold,
+              float* __restrict__ out) {
+    extern __shared__ float lds[];
+    // the strips of a pattern run on one XCD (workgroups go round the XCDs)
+    const int q = blockIdx.x / kXcds;
+    const int b = q / strips * kXcds + static_cast<int>(blockIdx.x) % kXcds;
+    if (b >= B) return;
+    const int x0 = (q % strips) * kTile;
+    const int r1 = f1.r, r2 = TWO ? f2.r : 0, R = max(r1, r2);
+    const int cols = kTile + 2 * R, cpitch = staged_pitch(R);
+    const int ring = ring_rows(R), ahead = blocks_ahead(R);
+    float* c = lds;                                   // [kTile][cpitch]
+    float* ring1 = c + kTile * cpitch;                // [ring][kTile]
+    float* ring2 = ring1 + ring * kTile;
+    float* t1 = TWO ? ring2 + ring * kTile : ring2;
+    float* t2 = t1 + table_len(r1);
+    uint32_t* bad = reinterpret_cast<uint32_t*>(TWO ? t2 + table_len(r2) : t2);   // [ring][4], then any
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ti = wave >> 1, tj = wave & 1;          // this wave's tile
+    const int m16 = lane & 15, k4 = lane >> 4;
+    for (int i = tid; i < table_len(r1); i += kThreads) {
+        const int d = abs(i - 15 - r1);
+        t1[i] = d <= r1 ? f1.w[d] : 0.0f;
+    }
+    if (TWO)
+        for (int i = tid; i < table_len(r2); i += kThreads) {
+            const int d = abs(i - 15 - r2);
+            t2[i] = d <= r2 ? f2.w[d] : 0.0f;
+        }
+    for (int i = tid; i <= 4 * ring; i += kThreads) bad[i] = 0u;
+    const Tin* img = in + static_cast<size_t>(b) * H * W;
+    // shift of the centred pattern: whole pixels and fractions
+    const double dx = centre ? centre[2 * b] - 0.5 * W : 0.0;
+    const double dy = centre ? centre[2 * b + 1] - 0.5 * H : 0.0;
+    const double xf = floor(dx), yf = floor(dy);
+    const float fx = static_cast<float>(dx - xf), fy = static_cast<float>(dy - yf);
+    const int sx = static_cast<int>(fmax(fmin(xf, 1e6), -1e6));
+    const int sy = static_cast<int>(fmax(fmin(yf, 1e6), -1e6));
+    const int n_blocks = (H + kTile - 1) / kTile;
+    constexpr int kRun = 8;                           // rows a thread stages in a column
+    const float inv_cols = 1.0f / static_cast<float>(cols);
+    float* dst = out + static_cast<size_t>(b) * H * W;
+    for (int blk = 0; blk < n_blocks + ahead; ++blk) {
+        if (blk < n_blocks) {
+            // ---- stage: tasks of one column and kRun rows
+            const int y0 = blk * kTile;
+            if constexpr (sizeof(Tin) == 4) {
+                __syncthreads();                      // the bits of this block's ring rows are free
+                if (tid < 4 * kTile) bad[4 * (y0 % ring) + tid] = 0u;
+                __syncthreads();
+            }
+            // all rows of the block inside the image: plain strides
+            const bool inside = y0 + sy >= 0 && y0 + sy + kTile < H;
+            for (int task = tid; task < cols * (kTile / kRun); task += kThreads) {
+                const int g = static_cast<int>((static_cast<float>(task) + 0.5f) * inv_cols);
+                const int i = task - g * cols;
+                const int x = mirror(x0 - R + i, W) + sx, ya = y0 + g * kRun + sy;
+                // a pair of neighbours inside the image and their weights
+                const int xp = min(max(x, 0), max(W - 2, 0));
+                const bool lo0 = x == xp && x < W, lo1 = x + 1 == xp, hi0 = x == xp + 1 && x < W, hi1 = x == xp && xp + 1 < W;
+                const float wl = lo0 ? 1.0f - fx : lo1 ? fx : 0.0f, wh = hi0 ? 1.0f - fx : hi1 ? fx : 0.0f;
+                // (byte offsets within a pattern fit 32 bits: H, W <= 8192)
+                const int second = W > 1 ? 1 : 0;
+                auto px = [&](int row, int o) {
+                    return static_cast<float>(*reinterpret_cast<const Tin*>(
+                        reinterpret_cast<const char*>(img) +
+                        static_cast<uint32_t>(row * W + xp + o) * static_cast<uint32_t>(sizeof(Tin))));
+                };
+                float a[kRun + 1];
+                auto blend = [&](float l, float h) {
+                    if constexpr (sizeof(Tin) == 4) {     // a pixel without weight may be non-finite
+                        l = wl != 0.0f ? l : 0.0f;
+                        h = wh != 0.0f ? h : 0.0f;
+                    }
+                    return wl * l + wh * h;
+                };
+                if (inside) {
+                    float l[kRun + 1], h[kRun + 1];
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                if (x + m < W) {
-                    out_a[base + x + m] = va[m];
-                    if (out_b) out_b[base + x + m] = vb[m];
+                    for (int u = 0; u <= kRun; ++u) {
+                        l[u] = px(ya + u, 0);
+                        h[u] = px(ya + u, second);
+                    }
+#pragma unroll
+                    for (int u = 0; u <= kRun; ++u) a[u] = blend(l[u], h[u]);
+                } else {
+#pragma unroll
+                    for (int u = 0; u <= kRun; ++u) {
+                        const int row = min(max(ya + u, 0), H - 1);
+                        const float v = blend(px(row, 0), px(row, second));
+                        a[u] = ya + u >= 0 && ya + u < H ? v : 0.0f;
+                    }
+                }
+                float* cp = c + g * kRun * cpitch + i;
+#pragma unroll
+                for (int u = 0; u < kRun; ++u) {
+                    float v = fy != 0.0f ? (1.0f - fy) * a[u] + fy * a[u + 1] : a[u];
+                    if (sizeof(Tin) == 4 && !(fabsf(v) <= 3.402823466e38f)) {
+                        // columns n within the reach of filter f; +inf and
+                        // -inf apart, NaN is both
+                        uint32_t* row = &bad[4 * ((y0 + g * kRun + u) % ring)];
+                        for (int f = 0; f < (TWO ? 2 : 1); ++f) {
+                            const int d = f ? f2.reach : f1.reach;
+                            const int n0 = max(0, i - R - d), n1 = min(kTile - 1, i - R + d);
+                            if (n0 > n1) continue;
+                            const uint32_t m = (0xffffffffu >> (31 - n1)) & (0xffffffffu << n0);
+                            if (!(v <= 0.0f)) atomicOr(row + 2 * f, m);
+                            if (!(v >= 0.0f)) atomicOr(row + 2 * f + 1, m);
+                        }
+                        bad[4 * ring] = 1u;
+                        v = 0.0f;
+                    }
+                    cp[u * cpitch] = v;
                 }
             }
-        }
-    }
-}
-
-// acc[i] += sum_t w[t] * L[(y + i + t) * 32 + c] for kTileRows / 8 rows i,
-// taps in blocks of kTapBlock: per block the weights are loaded once and a
-// window of rows + kTapBlock - 1 LDS values serves kTapBlock * rows FMAs
-// (weights past the radius are zero; the tile carries kTapBlock spare rows).
-template <int kRows>
-__device__ __forceinline__ void tap_block_col(const float* L, const Taps& tp, int y, int c,
-                                              float (&acc)[kRows]) {
-    for (int t0 = -tp.r; t0 <= tp.r; t0 += kTapBlock) {
-        float w[kTapBlock];
+            __syncthreads();
+            // ---- along x: tile (ti, tj) of both filters
+            const float* ca = c + (16 * ti + m16) * cpitch + 16 * tj + k4;
+            auto along_x = [&](const float* t, int r) {
+                const float *p = ca + (R - r), *w = t + 15 + k4 - m16;
+                return banded<4, 4>(r, [&](int k) { return p + k; }, [&](int k) { return w + k; },
+                                    [](int, int) { return true; });
+            };
+            const f32x4 a1 = along_x(t1, r1);
+            f32x4 a2 = a1;
+            if (TWO) a2 = along_x(t2, r2);
+            const int slot = y0 % ring;               // blocks do not straddle the ring's end
 #pragma unroll
-        for (int j = 0; j < kTapBlock; ++j) w[j] = t0 + j <= tp.r ? tp.w[t0 + j + tp.r] : 0.0f;
-        const float* p = L + (y + t0) * 32 + c;
-        float win[kRows + kTapBlock - 1];
-#pragma unroll
-        for (int i = 0; i < kRows + kTapBlock - 1; ++i) win[i] = p[i * 32];
-#pragma unroll
-        for (int j = 0; j < kTapBlock; ++j)
-#pragma unroll
-            for (int i = 0; i < kRows; ++i) acc[i] += w[j] * win[i + j];
-    }
-}
-
-// Correlation along y for a strip of 32 columns of an image at most
-// kTileRows high, held whole in LDS with a mirrored halo of rh rows:
-// out = G_a(ia) [- G_b(ib)], then the threshold. Threads: 32 columns x 8
-// row groups of kTileRows / 8 consecutive rows (rows of 128 bytes load
-// coalesced); the tap loop is the outer one, so each weight is loaded once
-// per thread and feeds 32 FMAs.
-__global__ void __launch_bounds__(kRowThreads)
-col_tile_kernel(const float* __restrict__ ia, const float* __restrict__ ib, int H, int W, Taps a,
-                Taps bt, int rh, bool thresh, float threshold, float* __restrict__ out) {
-    extern __shared__ float lds[];
-    constexpr int kRows = kTileRows / (kRowThreads / 32);
-    const int c = threadIdx.x & 31, g = threadIdx.x >> 5;
-    const int x = blockIdx.x * 32 + c, b = blockIdx.y;
-    const bool col_ok = x < W;
-    const int hp = kTileRows + 2 * rh + kTapBlock;
-    float* la = lds;
-    float* lb = lds + static_cast<size_t>(hp) * 32;
-    const size_t img = static_cast<size_t>(b) * H * W;
-    // staging: kStageBatch rows per thread loaded before any is stored, so
-    // their latencies overlap (every lane loads; columns past W read column
-    // 0 and store zeros)
-    constexpr int kGroups = kRowThreads / 32;
-    for (int i0 = g; i0 < hp; i0 += kGroups * kStageBatch) {
-        float va[kStageBatch], vb[kStageBatch];
-#pragma unroll
-        for (int u = 0; u < kStageBatch; ++u) {
-            const int i = min(i0 + kGroups * u, hp - 1);
-            const size_t src = img + static_cast<size_t>(mirror(i - rh, H)) * W + (col_ok ? x : 0);
-            va[u] = ia[src];
-            vb[u] = ib ? ib[src] : 0.0f;
-        }
-#pragma unroll
-        for (int u = 0; u < kStageBatch; ++u) {
-            const int i = i0 + kGroups * u;
-            if (i < hp) {
-                la[i * 32 + c] = col_ok ? va[u] : 0.0f;
-                if (ib) lb[i * 32 + c] = col_ok ? vb[u] : 0.0f;
+            for (int v = 0; v < 4; ++v) {
+                const int o = ring_at(slot + 16 * ti + 4 * k4 + v, 16 * tj + m16);
+                ring1[o] = a1[v];
+                if (TWO) ring2[o] = a2[v];
             }
         }
-    }
-    __syncthreads();
-    const int y0 = g * kRows;
-    if (!col_ok || y0 >= H) return;
-    float va[kRows], vb[kRows];
+        __syncthreads();
+        if (blk < ahead) continue;
+        // ---- along y: rows of block blk - ahead
+        const int y0 = (blk - ahead) * kTile + 16 * ti;
+        const int n = 16 * tj + m16;
+        auto along_y = [&](const float* rg, const float* t, int r) {
+            const float *w = t + 15 + k4 - m16, *lane_rg = rg + ring_at(k4, n);
+            auto tap = [&](int k) { return w + k; };
+            if (y0 >= r && y0 + 16 + r <= H) {        // uniform: no row is mirrored
+                // (4 | r, y0 and the ring: the 4 rows of a step lie together)
+                const int first = (y0 - r) % ring;
+                auto slot = [&](int k) { return first + k - (first + k >= ring ? ring : 0); };
+                return banded<4, 4 * kTile>(r, tap, [&](int k) { return lane_rg + slot(k) * kTile; },
+                                             [&](int k, int d) { return d > 0 ? slot(k) + 12 < ring : slot(k) >= 12; });
+            }
+            // (the rows in question lie within a ring's length of this one)
+            const int s0 = max(0, y0 - r) / ring * ring;
+            return banded<4, 0>(r, tap, [&](int k) {
+                int slot = mirror(y0 - r + k + k4, H) - s0;
+                slot += slot < 0 ? ring : 0;
+                slot -= slot >= ring ? ring : 0;
+                return rg + ring_at(slot, n);
+            }, [](int, int) { return false; });
+        };
+        f32x4 acc = along_y(ring1, t1, r1);
+        if (TWO) acc -= along_y(ring2, t2, r2);
+        const bool any_bad = sizeof(Tin) == 4 && bad[4 * ring] != 0u;
 #pragma unroll
-    for (int i = 0; i < kRows; ++i) va[i] = vb[i] = 0.0f;
-    tap_block_col(la, a, y0 + rh, c, va);
-    if (ib) tap_block_col(lb, bt, y0 + rh, c, vb);
-#pragma unroll
-    for (int i = 0; i < kRows; ++i) {
-        if (y0 + i >= H) break;
-        float v = ib ? va[i] - vb[i] : va[i];
-        if (thresh && v < threshold) v = 0.0f;
-        out[img + static_cast<size_t>(y0 + i) * W + x] = v;
-    }
-}
-
-// Correlation along y for any height (one thread per column, coalesced rows):
-// out = G_a(ia) [- G_b(ib)], then the threshold.
-__global__ void __launch_bounds__(kRowThreads)
-col_kernel(const float* __restrict__ ia, const float* __restrict__ ib, int H, int W, Taps a,
-           Taps bt, bool thresh, float threshold, float* __restrict__ out) {
-    const int x = blockIdx.x * kRowThreads + threadIdx.x;
-    const int b = blockIdx.y;
-    if (x >= W) return;
-    const size_t img = static_cast<size_t>(b) * H * W;
-    for (int y = 0; y < H; ++y) {
-        float v = 0.0f;
-        for (int t = -a.r; t <= a.r; ++t) v += a.w[t + a.r] * ia[img + static_cast<size_t>(mirror(y + t, H)) * W + x];
-        if (ib) {
-            float u = 0.0f;
-            for (int t = -bt.r; t <= bt.r; ++t) u += bt.w[t + bt.r] * ib[img + static_cast<size_t>(mirror(y + t, H)) * W + x];
-            v -= u;
+        for (int v = 0; v < 4; ++v) {
+            const int y = y0 + 4 * k4 + v, x = x0 + n;
+            float z = acc[v];
+            if (any_bad && y < H) {
+                auto reached = [&](int f, int reach) {
+                    uint32_t pos = 0, neg = 0;
+                    for (int d = -reach; d <= reach; ++d) {
+                        const uint32_t* row = &bad[4 * (mirror(y + d, H) % ring) + 2 * f];
+                        pos |= row[0];
+                        neg |= row[1];
+                    }
+                    const float inf = __int_as_float(0x7f800000);
+                    return ((pos >> n) & 1u ? inf : 0.0f) - ((neg >> n) & 1u ? inf : 0.0f);
+                };
+                z += reached(0, f1.reach);
+                if (TWO) z -= reached(1, f2.reach);
+            }
+            if (thresh && z < threshold) z = 0.0f;
+            if (y < H && x < W) dst[static_cast<size_t>(y) * W + x] = z;
         }
-        if (thresh && v < threshold) v = 0.0f;
-        out[img + static_cast<size_t>(y) * W + x] = v;
     }
 }
 
-void pad_taps(Taps& t) {
-    const int r4 = (t.r + 3) & ~3;
-    for (int i = 0; i < kWLen; ++i) {
-        const int k = i - r4;
-        t.wp[i] = (k >= -t.r && k <= t.r) ? t.w[k + t.r] : 0.0f;
-    }
+// Normalised taps of G(sigma) in float64, w[r + t] for |t| <= r (sigma 0: the
+// identity); returns r.
+int gaussian(double sigma, double (&w)[2 * kMaxRadius + 1]) {
+    const int r = sigma > 0.0 ? static_cast<int>(4.0 * sigma + 0.5) : 0;
+    double s = 0.0;
+    for (int i = -r; i <= r; ++i) s += w[i + r] = r ? std::exp(-static_cast<double>(i) * i / (2.0 * sigma * sigma)) : 1.0;
+    for (int i = 0; i <= 2 * r; ++i) w[i] /= s;
+    return r;
 }
 
-bool make_taps(double sigma, Taps& t) {
-    t = Taps{};
-    if (!(sigma > 0.0)) {
-        t.r = 0;
-        t.w[0] = 1.0f;
-        pad_taps(t);
-        return true;
+// The filter G(a) G(b).
+Filter make_filter(double a, double b) {
+    double u[2 * kMaxRadius + 1], v[2 * kMaxRadius + 1];
+    const int ru = gaussian(a, u), rv = gaussian(b, v);
+    Filter f{};
+    f.reach = ru + rv;
+    f.r = (f.reach + 3) & ~3;
+    for (int t = 0; t <= f.reach; ++t) {
+        double w = 0.0;
+        for (int i = std::max(-ru, t - rv); i <= std::min(ru, t + rv); ++i) w += u[i + ru] * v[t - i + rv];
+        f.w[t] = static_cast<float>(w);
     }
-    const int r = static_cast<int>(4.0 * sigma + 0.5);
-    if (r > kMaxRadius) return false;
-    double w[2 * kMaxRadius + 1], s = 0.0;
-    for (int i = -r; i <= r; ++i) {
-        w[i + r] = std::exp(-static_cast<double>(i) * i / (2.0 * sigma * sigma));
-        s += w[i + r];
-    }
-    t.r = r;
-    for (int i = 0; i <= 2 * r; ++i) t.w[i] = static_cast<float>(w[i] / s);
-    pad_taps(t);
-    return true;
+    return f;
 }
 
 template <typename Tin>
 int run(const Tin* in, int B, int H, int W, const tm_preprocess_opts& o, float* out,
         double* centre_out, hipStream_t s) {
-    Taps ta, tb, tblur, tid;
-    if (!make_taps(o.sigma_min, ta) || !make_taps(o.sigma_max, tb) ||
-        !make_taps(o.sigma_blur, tblur)) {
-        tmlib::set_error("Gaussian sigma above %g (radius %d)", (kMaxRadius - 0.5) / 4.0, kMaxRadius);
-        return TM_EINVAL;
-    }
-    make_taps(0.0, tid);
     const bool dog = o.sigma_max > 0.0;
-    const bool thresh = std::isfinite(o.threshold);
-    const size_t img = static_cast<size_t>(H) * W;
-    const int chunk = static_cast<int>(std::max<size_t>(
-        1, std::min<size_t>({static_cast<size_t>(B), kScratchBudget / (2 * img * 4), size_t(65535)})));
-    float* s1 = nullptr;
-    float* s2 = nullptr;
-    double* cen = nullptr;
-    hipError_t e = hipMallocAsync(reinterpret_cast<void**>(&s1), img * 4 * chunk, s);
-    if (e == hipSuccess) e = hipMallocAsync(reinterpret_cast<void**>(&s2), img * 4 * chunk, s);
-    if (e == hipSuccess && !centre_out) e = hipMallocAsync(reinterpret_cast<void**>(&cen), 16 * static_cast<size_t>(B), s);
-    int r = TM_OK;
-    if (e != hipSuccess) r = tmlib::hip_fail(e, "hipMallocAsync");
-    double* cptr = centre_out ? centre_out : cen;
-    // LDS: rows with a mirrored halo (any W up to 8192 fits), column strips
-    // of the full height when they fit, else the per-column kernel
-    const int rh1 = dog ? std::max(ta.r, tb.r) : 0, rhb = tblur.r;
-    // row halos rounded up to multiples of 4 (aligned tap windows)
-    const int rr1 = (rh1 + 3) & ~3, rrb = (rhb + 3) & ~3;
-    const size_t row_lds1 = static_cast<size_t>(kRowWaves) * row_strip(W, rr1) * sizeof(float);
-    const size_t row_ldsb = static_cast<size_t>(kRowWaves) * row_strip(W, rrb) * sizeof(float);
-    const size_t col_lds1 =
-        static_cast<size_t>(kTileRows + 2 * rh1 + kTapBlock) * 32 * sizeof(float) * (dog ? 2 : 1);
-    const size_t col_ldsb = static_cast<size_t>(kTileRows + 2 * rhb + kTapBlock) * 32 * sizeof(float);
-    const bool tile1 = H <= kTileRows && col_lds1 <= kLdsLimit;
-    const bool tileb = H <= kTileRows && col_ldsb <= kLdsLimit;
-    if (r == TM_OK) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(row_kernel<Tin>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(row_lds1));
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(row_kernel<float>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    static_cast<int>(std::max(row_ldsb, row_lds1)));
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(col_tile_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    static_cast<int>(std::min(kLdsLimit, std::max(col_lds1, col_ldsb))));
-        if (e != hipSuccess) r = tmlib::hip_fail(e, "hipFuncSetAttribute");
-    }
-    const dim3 rgrid((H + kRowWaves - 1) / kRowWaves, 1);
-    const dim3 tgrid((W + 31) / 32, 1);
-    const dim3 cgrid((W + kRowThreads - 1) / kRowThreads, 1);
-    const bool blur = o.sigma_blur > 0.0;
-    for (int b0 = 0; r == TM_OK && b0 < B; b0 += chunk) {
-        const int nb = std::min(chunk, B - b0);
-        const Tin* cin = in + static_cast<size_t>(b0) * img;
-        float* cout = out + static_cast<size_t>(b0) * img;
-        double* cc = cptr + 2 * static_cast<size_t>(b0);
-        if (o.r_box >= 0 || centre_out) {
-            // with r_box < 0 the box is empty and the centre is (W/2, H/2)
-            hipLaunchKernelGGL(centre_kernel<Tin>, dim3(nb), dim3(kCentreThreads), 0, s, cin, H, W,
+    const Filter f1 = make_filter(dog ? o.sigma_min : 0.0, o.sigma_blur);
+    const Filter f2 = dog ? make_filter(o.sigma_max, o.sigma_blur) : Filter{};
+    double* cen = centre_out;
+    tmlib::Scratch mem;
+    if (!cen && o.r_box >= 0) mem.add(cen, 2 * static_cast<size_t>(B));
+    const bool scratch = !centre_out && o.r_box >= 0;
+    if (scratch)
+        if (int r = mem.allocate(s)) return r;
+    const int R = std::max(f1.r, f2.r), ring = ring_rows(R);
+    const size_t lds = sizeof(float) *
+                       (static_cast<size_t>(kTile) * staged_pitch(R) +
+                        static_cast<size_t>(ring) * kTile * (dog ? 2 : 1) + table_len(f1.r) +
+                        (dog ? table_len(f2.r) : 0) + 4 * ring + 1);
+    auto kern = dog ? filter_kernel<Tin, true> : filter_kernel<Tin, false>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+    const int strips = (W + kTile - 1) / kTile;
+    const int chunk = kMaxGrid / (strips * kXcds) * kXcds;    // patterns of a launch
+    for (int b0 = 0; e == hipSuccess && b0 < B; b0 += chunk) {
+        const int n = std::min(chunk, B - b0);
+        const Tin* cin = in + static_cast<size_t>(b0) * H * W;
+        double* cc = cen ? cen + 2 * static_cast<size_t>(b0) : nullptr;
+        if (cc)    // with r_box < 0 the box is empty and the centre is (W/2, H/2)
+            hipLaunchKernelGGL(centre_kernel<Tin>, dim3(n), dim3(kCentreThreads), 0, s, cin, H, W,
                                o.r_box, o.frac, cc);
-        }
-        // centred rows, correlated along x with G(sigma_min) and G(sigma_max)
-        hipLaunchKernelGGL(row_kernel<Tin>, dim3(rgrid.x, nb), dim3(kRowThreads), row_lds1, s, cin,
-                           static_cast<const float*>(nullptr), o.r_box >= 0 ? cc : nullptr, H, W,
-                           dog ? ta : tid, tb, rr1, s1, dog ? s2 : nullptr);
-        // along y: difference of Gaussians (or the plain centred image) -> out
-        if (tile1)
-            hipLaunchKernelGGL(col_tile_kernel, dim3(tgrid.x, nb), dim3(kRowThreads), col_lds1, s,
-                               s1, dog ? s2 : nullptr, H, W, dog ? ta : tid, tb, rh1,
-                               !blur && thresh, static_cast<float>(o.threshold), cout);
-        else
-            hipLaunchKernelGGL(col_kernel, dim3(cgrid.x, nb), dim3(kRowThreads), 0, s, s1,
-                               dog ? s2 : nullptr, H, W, dog ? ta : tid, tb, !blur && thresh,
-                               static_cast<float>(o.threshold), cout);
-        if (blur) {
-            // rows of the difference image (now in out) -> s1, then columns -> out
-            hipLaunchKernelGGL(row_kernel<float>, dim3(rgrid.x, nb), dim3(kRowThreads), row_ldsb, s,
-                               static_cast<const float*>(nullptr), static_cast<const float*>(cout),
-                               static_cast<const double*>(nullptr), H, W, tblur, tid, rrb, s1,
-                               static_cast<float*>(nullptr));
-            if (tileb)
-                hipLaunchKernelGGL(col_tile_kernel, dim3(tgrid.x, nb), dim3(kRowThreads), col_ldsb,
-                                   s, s1, static_cast<const float*>(nullptr), H, W, tblur, tid,
-                                   rhb, thresh, static_cast<float>(o.threshold), cout);
-            else
-                hipLaunchKernelGGL(col_kernel, dim3(cgrid.x, nb), dim3(kRowThreads), 0, s, s1,
-                                   static_cast<const float*>(nullptr), H, W, tblur, tid, thresh,
-                                   static_cast<float>(o.threshold), cout);
-        }
+        hipLaunchKernelGGL(kern, dim3((n + kXcds - 1) / kXcds * kXcds * strips), dim3(kThreads), lds, s,
+                           cin, o.r_box >= 0 ? cc : nullptr, n, H, W, strips, f1, f2,
+                           static_cast<bool>(std::isfinite(o.threshold)), static_cast<float>(o.threshold),
+                           out + static_cast<size_t>(b0) * H * W);
         e = hipGetLastError();
-        if (e != hipSuccess) r = tmlib::hip_fail(e, "preprocess kernel launch");
+        if (b0 > B - chunk) break;                            // (b0 stays in int)
     }
-    if (s1) (void)hipFreeAsync(s1, s);
-    if (s2) (void)hipFreeAsync(s2, s);
-    if (cen) (void)hipFreeAsync(cen, s);
-    return r;
+    const int r = e == hipSuccess ? TM_OK : tmlib::hip_fail(e, "preprocess kernel launch");
+    return scratch ? mem.release(s, r) : r;
 }
 
 }  // namespace

@@ -149,3 +149,49 @@ def test_centring_restores_indexing_of_offset_patterns(tm, c1, c1_lib):
     a_off, a_cen = np.mean(t_off == t_ref), np.mean(t_cen == t_ref)
     _say(f"top-1 as the unmoved patterns: off-centre {a_off:.2f}, centred {a_cen:.2f}")
     assert a_cen >= 0.8 and a_cen > a_off
+
+
+# Around the 32-column strips and the 32-row blocks, 16-row tiles and the ring
+# of filtered rows; reaches 0, 6 (taps padded to 8), 28 and the largest, 128.
+@pytest.mark.parametrize("shape", [(31, 33), (32, 32), (33, 31), (48, 65), (161, 40), (400, 17)])
+@pytest.mark.parametrize("sigmas", [(0.0, 0.0, 0.0), (0.5, 0.9, 0.5), (1.0, 6.0, 1.0),
+                                    (3.0, 15.9, 15.9)])
+def test_preprocess_edges_of_strips_and_blocks(tm, shape, sigmas):
+    """Plain float64 reference of the whole chain; the bound is the file's."""
+    import torch
+    rng = np.random.default_rng(95)
+    imgs = (rng.random((9,) + shape) * 2.0).astype(np.float32)     # 9: one over a group of 8
+    o = dict(r_box=3, frac=0.4, sigma_min=sigmas[0], sigma_max=sigmas[1], sigma_blur=sigmas[2],
+             threshold=float("-inf"))
+    _say("preprocess strips", shape, sigmas)
+    out, cen = tm.preprocess(torch.from_numpy(imgs).cuda(), **o)
+    out = out.cpu().numpy()
+    for b in (0, 7, 8):
+        want, _ = oracle.preprocess64(imgs[b].astype(np.float64), **o)
+        _compare(out[b], want, want, o["threshold"], (shape, sigmas, b))
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("sigmas", [(0.0, 0.0, 0.0), (0.0, 0.0, 0.9), (1.0, 2.0, 0.5)])
+def test_preprocess_nonfinite_pixels_reach_as_far_as_the_taps(tm, bad, sigmas):
+    """One non-finite pixel: infinite or NaN outputs where the reference's
+    are, and elsewhere the values of the image without it."""
+    import torch
+    rng = np.random.default_rng(97)
+    shape, at = (75, 70), [(0, 0), (40, 31), (74, 69), (33, 64)]
+    imgs = rng.random((len(at),) + shape).astype(np.float32)
+    for b, (y, x) in enumerate(at):
+        imgs[b, y, x] = bad
+    o = dict(r_box=-1, frac=0.4, sigma_min=sigmas[0], sigma_max=sigmas[1], sigma_blur=sigmas[2],
+             threshold=float("-inf"))
+    _say("preprocess non-finite", bad, sigmas)
+    out, _ = tm.preprocess(torch.from_numpy(imgs).cuda(), **o)
+    out = out.cpu().numpy()
+    for b, (y, x) in enumerate(at):
+        with np.errstate(invalid="ignore"):
+            want, _ = oracle.preprocess64(imgs[b].astype(np.float64), **o)
+        assert np.array_equal(np.isnan(out[b]), np.isnan(want)), (b, at[b])
+        inf = np.isinf(want)
+        assert np.array_equal(out[b][inf], want[inf]) and np.array_equal(np.isinf(out[b]), inf)
+        ok = np.isfinite(want)
+        _compare(out[b][ok], want[ok], want[ok], o["threshold"], (bad, sigmas, b))
