@@ -41,13 +41,16 @@
 //
 // Quarter-turn pairing. A pixel at column k = q win + r (q = 0..3, r <
 // win) needs M at r + (q + S) win for S = 0..3, the 4 maxima M[r + i win],
-// i = 0..3, in some rotation. The window image stores them as two dwords,
+// i = 0..3, in some rotation. The window image stores them as one entry,
 //
-//   Y[j, r] = (M[j, r], M[j, r + 2 win]),  Y[j, r + win] = (M[j, r + win],
-//   M[j, r + 3 win])                         (float16 each, columns mod n),
+//   Y[j, r] = (M[j, r], M[j, r + 2 win], M[j, r + win], M[j, r + 3 win])
+//                                            (float16 each, columns mod n),
 //
-// one row of 2 win dwords (plus one unused, for an odd pitch) per touched
-// row, read with one 2-dword LDS read at r and r + win. acc[i] collects
+// one row of win entries (plus one unused where win is even, for an odd
+// pitch) per touched row, read with one aligned 8-byte LDS read. That costs
+// half of two 4-byte ones from the same instruction (2.6 against 4.7 clk per
+// wave without bank conflicts; a half-wave reads 32 banks of 8 bytes at a
+// time, and a conflict is met once, not twice). acc[i] collects
 // M[r + i win], which is shift S = i - q (mod 4): the pixels of one quarter
 // share the rotation. A lane takes its
 // template's quarters in cyclic order (its largest first); between two
@@ -75,13 +78,17 @@
 //   * each template's margin term (below) is one more record: its weight
 //     the margin factor, its window maxima read from an extra image row
 //     that holds the largest |P| (scaled, rounded up) everywhere;
-//   * per record: one address multiply-add, one 2-dword LDS read (two
-//     pairs of float16 window maxima) and 4 mixed float16 x float16 +
-//     float32 multiply-adds; the library orders each step's records over the
+//   * per record: one address multiply-add, one 8-byte LDS read (four
+//     float16 window maxima) and 4 mixed float16 x float16 + float32
+//     multiply-adds; the library orders each step's records over the
 //     lanes so that the reads of a half-wave fall on distinct LDS banks (or
-//     the same dword) where possible;
+//     the same entry) where possible;
 //   * a chunk's bounds leave as one coalesced 256-byte store, in chunk-slot
 //     order (the library's slot -> template map goes with them).
+//
+// Bound: vector issue (5.7 instructions per record, one per clock and CU).
+// 16 384 patterns, 20 000 templates of 76 spots on average: 10.8 ms; 11.9 ms
+// with two 4-byte reads per record, which kept the LDS busy 96 % of the time.
 #include <algorithm>
 #include <array>
 #include <cmath>
@@ -96,7 +103,7 @@ namespace {
 constexpr int kShifts = 4;                 // coarse shifts per template
 constexpr int kLanes = 64;                 // templates per chunk, one per lane
 constexpr int kUnitSteps = 4;              // records per lane and unit (one 16-byte load)
-constexpr int kBanks = 32;                 // LDS banks of 4 bytes, per half-wave
+constexpr int kBanks = 32;                 // LDS banks of 8 bytes, per half-wave
 constexpr int kChoices = 64;               // records tried per lane and step
 constexpr int kWeightExp = 10;             // float16 weights carry w * 2^10
 constexpr int kImageExp = 14;              // window maxima scaled below 2^14
@@ -144,9 +151,10 @@ size_t scratch_halves(int n, int win) {
 
 // ---------------------------------------------------------------- device side
 
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) const uint16_t lds_u16;
-typedef __attribute__((address_space(3))) const uint32_t lds_u32;
+typedef __attribute__((address_space(3))) const u32x2 lds_u32x2;
 
 __device__ __forceinline__ float h2f(uint32_t bits16) {
     return static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(bits16)));
@@ -160,49 +168,40 @@ __device__ __forceinline__ uint16_t f16_up(float x) {
     return b;
 }
 
-// LDS byte address of a record's first pair: the record's 16-bit dword
-// offset times 4 plus the image base, in one multiply-add of the low 16
-// bits (v_mad_u32_u16).
+// LDS byte address of a record's entry: the record's 16-bit entry number
+// times 8 plus the image base, in one multiply-add of the low 16 bits
+// (v_mad_u32_u16).
 __device__ __forceinline__ uint32_t rec_addr(uint32_t rec, uint32_t base) {
     uint32_t a;
-    asm("v_mad_u32_u16 %0, %1, 4, %2" : "=v"(a) : "v"(rec), "v"(base));
+    asm("v_mad_u32_u16 %0, %1, 8, %2" : "=v"(a) : "v"(rec), "v"(base));
     return a;
 }
 
-constexpr int kPairs = 2;                  // 32-bit LDS reads per record
-
-// The LDS reads of one unit of a lane's records (4 steps): the two pairs of
-// each record (win dwords apart), issued without waiting; the address uses
-// only a record's low 16 bits.
-template <int WIN>
-__device__ __forceinline__ void read_unit(const u32x4 R, uint32_t base, int win,
-                                          uint32_t (&v)[kUnitSteps * kPairs]) {
+// The LDS reads of one unit of a lane's records (4 steps), issued without
+// waiting; the address uses only a record's low 16 bits.
+__device__ __forceinline__ void read_unit(const u32x4 R, uint32_t base, u32x2 (&v)[kUnitSteps]) {
 #pragma unroll
-    for (int u = 0; u < kUnitSteps; ++u) {
-        lds_u32* p = reinterpret_cast<lds_u32*>(static_cast<uintptr_t>(rec_addr(R[u], base)));
-        v[u * kPairs] = p[0];
-        v[u * kPairs + 1] = p[WIN ? WIN : win];
-    }
+    for (int u = 0; u < kUnitSteps; ++u)
+        v[u] = *reinterpret_cast<lds_u32x2*>(static_cast<uintptr_t>(rec_addr(R[u], base)));
 }
 
 // The multiply-adds of one unit: acc[0], acc[2] from the first pair's low
 // and high halves, acc[1], acc[3] from the second's.
-__device__ __forceinline__ void fma_unit(const u32x4 R, const uint32_t (&v)[kUnitSteps * kPairs],
+__device__ __forceinline__ void fma_unit(const u32x4 R, const u32x2 (&v)[kUnitSteps],
                                          float (&acc)[kShifts]) {
 #pragma unroll
     for (int u = 0; u < kUnitSteps; ++u) {
         const float w = h2f(R[u] >> 16);
-        acc[0] = fmaf(w, h2f(v[u * kPairs]), acc[0]);
-        acc[2] = fmaf(w, h2f(v[u * kPairs] >> 16), acc[2]);
-        acc[1] = fmaf(w, h2f(v[u * kPairs + 1]), acc[1]);
-        acc[3] = fmaf(w, h2f(v[u * kPairs + 1] >> 16), acc[3]);
+        acc[0] = fmaf(w, h2f(v[u].x), acc[0]);
+        acc[2] = fmaf(w, h2f(v[u].x >> 16), acc[2]);
+        acc[1] = fmaf(w, h2f(v[u].y), acc[1]);
+        acc[3] = fmaf(w, h2f(v[u].y >> 16), acc[3]);
     }
 }
 
-// WIN > 0: win as a constant (the second read's offset becomes an
-// immediate of the LDS instruction); 0: taken from win. Image rows are Lrow
-// (= 2 win + 1) dwords, place r holding compact row rowat[r]; wlen is the
-// width of the window maxima.
+// WIN > 0: win as a constant (fewer columns per lane in the build); 0: taken
+// from win. Image rows are Lrow (at least win) entries, place r holding
+// compact row rowat[r]; wlen is the width of the window maxima.
 template <int NW, int WIN>
 __global__ void __launch_bounds__(NW * 64, (NW == 16 && WIN) ? 8 : 1)
 bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, int Rs, int n,
@@ -274,8 +273,8 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
     // consecutive columns x0 = o l .. x0 + o - 1: the part every window
     // shares (column x0 + o - 1, q whole blocks, r more columns), then the
     // head's suffix maxima and the tail's prefix maxima. Column x is the low
-    // half of Y[x] (if x < Lrow) and the high half of Y[c], c + 2 win = x
-    // (mod n), if c < Lrow (Lrow = 2 win <= n: at most one of each). The
+    // half of pair x (if x < 2 win) and the high half of pair c, c + 2 win = x
+    // (mod n), if c < 2 win (2 win <= n: at most one of each). The
     // next row's loads are issued before the current row is processed; the
     // buffers are the wave's own (wave-level ordering only).
     const int o = (n + 63) / 64;                 // columns per lane (<= MC)
@@ -283,7 +282,7 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
     const int nb = (n + H) / o;                  // whole blocks in rb
     const int q = (wlen - o) / o, rq = wlen - o - q * o;
     constexpr int PW = NW < kBuildWaves ? NW : kBuildWaves;   // waves that build rows
-    uint16_t* rb = m16 + static_cast<size_t>(n_rows + 1) * Lrow * 2 +
+    uint16_t* rb = m16 + static_cast<size_t>(n_rows + 1) * Lrow * 4 +
                    static_cast<size_t>(wave) * scr_stride;
     uint16_t* bm = rb + n + H;
     // image row place r holds compact row rowat[r]
@@ -319,7 +318,7 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
             bm[bk] = static_cast<uint16_t>(m);
         }
         tmlib::wave_sync();
-        uint16_t* dst = m16 + static_cast<size_t>(r) * Lrow * 2;
+        uint16_t* dst = m16 + static_cast<size_t>(r) * Lrow * 4;
         const int x0 = o * lane;
         if (x0 < n) {
             uint32_t hv[MC], tv[MC];
@@ -349,9 +348,10 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
                 const int x = x0 + d;
                 if (d < o && x < n) {
                     const uint16_t h = static_cast<uint16_t>(out[d]);
-                    if (x < Lrow) dst[2 * x] = h;
+                    auto at = [&](int c) { return c < win ? 4 * c : 4 * (c - win) + 2; };
+                    if (x < 2 * win) dst[at(x)] = h;
                     const int c = x - 2 * win + (x < 2 * win ? n : 0);
-                    if (c < Lrow) dst[2 * c + 1] = h;
+                    if (c < 2 * win) dst[at(c) + 1] = h;
                 }
             }
         }
@@ -361,8 +361,8 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
     // the extra row n_rows: A scaled, rounded up (the margin records' value)
     {
         const uint16_t h = f16_up(A * scale);
-        uint16_t* dst = m16 + static_cast<size_t>(n_rows) * Lrow * 2;
-        for (int x = threadIdx.x; x < 2 * Lrow; x += NW * 64) dst[x] = h;
+        uint16_t* dst = m16 + static_cast<size_t>(n_rows) * Lrow * 4;
+        for (int x = threadIdx.x; x < 4 * Lrow; x += NW * 64) dst[x] = h;
     }
     __syncthreads();
     // 3. bounds: per template Q^ = ((m out_scale) dfac) invP (1 + 2^-19), m
@@ -428,7 +428,7 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
     // quarter slot but the last the accumulators rotate by one (the value of
     // shift S moves from acc[S + q] to acc[S + q + 1], mod 4); at the chunk's
     // end its bounds (one coalesced store) and fresh accumulators
-    auto consume = [&](const u32x4 R, const uint32_t (&v)[kUnitSteps * kPairs], int uu) {
+    auto consume = [&](const u32x4 R, const u32x2 (&v)[kUnitSteps], int uu) {
         fma_unit(R, v, acc);
         if (uu == s0) {
             do {
@@ -470,30 +470,30 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
     u32x4 g1 = ld(u_begin + 1);
     u32x4 g2 = ld(u_begin + 2);
     u32x4 g3 = ld(u_begin + 3);
-    uint32_t va[kUnitSteps * kPairs], vb[kUnitSteps * kPairs];
+    u32x2 va[kUnitSteps], vb[kUnitSteps];
 #define TM_BOUND_SB __builtin_amdgcn_sched_barrier(0)
     int u = u_begin;
     for (; u + 8 <= u_end; u += 8) {
-        read_unit<WIN>(g0, base, win, va); TM_BOUND_SB;
-        read_unit<WIN>(g1, base, win, vb); TM_BOUND_SB;
+        read_unit(g0, base, va); TM_BOUND_SB;
+        read_unit(g1, base, vb); TM_BOUND_SB;
         consume(g0, va, u); g0 = ld(u + 4); TM_BOUND_SB;
-        read_unit<WIN>(g2, base, win, va); TM_BOUND_SB;
+        read_unit(g2, base, va); TM_BOUND_SB;
         consume(g1, vb, u + 1); g1 = ld(u + 5); TM_BOUND_SB;
-        read_unit<WIN>(g3, base, win, vb); TM_BOUND_SB;
+        read_unit(g3, base, vb); TM_BOUND_SB;
         consume(g2, va, u + 2); g2 = ld(u + 6); TM_BOUND_SB;
-        read_unit<WIN>(g0, base, win, va); TM_BOUND_SB;
+        read_unit(g0, base, va); TM_BOUND_SB;
         consume(g3, vb, u + 3); g3 = ld(u + 7); TM_BOUND_SB;
-        read_unit<WIN>(g1, base, win, vb); TM_BOUND_SB;
+        read_unit(g1, base, vb); TM_BOUND_SB;
         consume(g0, va, u + 4); g0 = ld(u + 8); TM_BOUND_SB;
-        read_unit<WIN>(g2, base, win, va); TM_BOUND_SB;
+        read_unit(g2, base, va); TM_BOUND_SB;
         consume(g1, vb, u + 5); g1 = ld(u + 9); TM_BOUND_SB;
-        read_unit<WIN>(g3, base, win, vb); TM_BOUND_SB;
+        read_unit(g3, base, vb); TM_BOUND_SB;
         consume(g2, va, u + 6); g2 = ld(u + 10); TM_BOUND_SB;
         consume(g3, vb, u + 7); g3 = ld(u + 11); TM_BOUND_SB;
     }
     // the last 0..7 units, one at a time
     auto process = [&](u32x4 R, int uu) {
-        read_unit<WIN>(R, base, win, va);
+        read_unit(R, base, va);
         consume(R, va, uu);
     };
     for (; u + 4 <= u_end; u += 4) {
@@ -539,27 +539,28 @@ int tmlib::bound_prepare(tm_library* L, const std::vector<std::vector<HostPixel>
     // (n_theta >= 16, so that 2 win <= n_theta)
     if (n < 16) return TM_OK;
     const int win = (n + kShifts - 1) / kShifts;
-    // window image rows of 2 win dwords (pairs of float16 window maxima),
-    // read at r and r + win, plus one unused dword: an odd pitch, so that a
-    // row's place in the image sets the LDS bank of its column 0 to any of
-    // the 32 (rows are placed below to even out the banks)
-    const int Lrow = 2 * win + 1;
-    // rows: the touched ones, then one holding A (the margin records' value)
-    const size_t dwords = static_cast<size_t>(L->n_rows + 1) * Lrow;
+    // window image rows of win entries (4 float16 window maxima), of an odd
+    // number where it fits, so that a row's place in the image sets the LDS
+    // bank of its column 0 to any of the 32 (rows are placed below to even
+    // out the banks); the touched rows, then one holding A (the margin
+    // records' value)
+    const size_t dwords = static_cast<size_t>(L->n_rows + 1) * (2 * win + 1);
     if (dwords * 4 > kLdsBudget || dwords > 65536) return TM_OK;   // window image too large
     // with the row buffers of the waves that build it, the workgroup's LDS
     // must fit the device's
+    int Lrow = win;
     {
         int dev = 0, max_lds = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
             return TM_OK;
-        if (dwords * 4 + kBuildWaves * 2 * scratch_halves(n, win) > static_cast<size_t>(max_lds))
-            return TM_OK;
+        const size_t build = kBuildWaves * 2 * scratch_halves(n, win), odd = win | 1;
+        if (dwords * 4 + build > static_cast<size_t>(max_lds)) return TM_OK;
+        if ((L->n_rows + 1) * odd * 8 + build <= static_cast<size_t>(max_lds)) Lrow = win | 1;
     }
     const uint32_t a_row = static_cast<uint32_t>(L->n_rows) * Lrow;
 
-    // per template and quarter-turn q = k / win: records (dword offset of
+    // per template and quarter-turn q = k / win: records (entry number of
     // column k - q win, float16 weight); the margin record joins the
     // smallest quarter; the lane's order of quarters is the rotation
     // (starting quarter o, then o + 1, ... mod 4) that puts the most
@@ -700,10 +701,8 @@ int tmlib::bound_prepare(tm_library* L, const std::vector<std::vector<HostPixel>
     }
     std::vector<int32_t> cend(n_chunks, 0), send(static_cast<size_t>(n_chunks) * 4, 0);
     std::vector<uint32_t> recs;
-    // LDS bank model of the pair reads: kBanks banks of 4 bytes, lanes
-    // grouped in half-waves; the dword of a record's read r
-    const int nbanks = kBanks, group = kLanes / 2;
-    auto dword = [&](uint32_t rec, int r) { return (rec & 0xffffu) + r * static_cast<uint32_t>(win); };
+    // LDS bank model of the entry reads: lanes in half-waves
+    const int group = kLanes / 2;
     auto whole = [](int m) { return (m + kUnitSteps - 1) / kUnitSteps * kUnitSteps; };
     for (int32_t c = 0; c < n_chunks; ++c) {
         int mh[kShifts] = {0, 0, 0, 0};
@@ -730,29 +729,20 @@ int tmlib::bound_prepare(tm_library* L, const std::vector<std::vector<HostPixel>
             for (int l = 0; l < kLanes; ++l)
                 if (tid[c * kLanes + l] >= 0) left[l] = tr[tid[c * kLanes + l]][p];
             for (int i = sb[p]; i < sb[p + 1]; ++i) {
-                // per read and bank: the first dword read there and the
-                // number of distinct dwords (a second lane on the same dword
-                // is free)
-                std::vector<uint32_t> first(static_cast<size_t>(kPairs) * nbanks);
-                std::vector<uint8_t> ndist(static_cast<size_t>(kPairs) * nbanks);
+                // per bank: the first entry read there and the number of
+                // distinct entries (a second lane on the same one is free)
+                std::array<uint32_t, kBanks> first{};
+                std::array<uint8_t, kBanks> ndist{};
                 for (int l = 0; l < kLanes; ++l) {
                     if (l % group == 0) std::fill(ndist.begin(), ndist.end(), 0);
-                    auto cost = [&](uint32_t rec) {
-                        int k = 0;
-                        for (int r = 0; r < kPairs; ++r) {
-                            const uint32_t d = dword(rec, r);
-                            const size_t ix = static_cast<size_t>(r) * nbanks + d % nbanks;
-                            if (ndist[ix] && first[ix] != d) k += ndist[ix];
-                        }
-                        return k;
+                    auto cost = [&](uint32_t rec) -> int {
+                        const uint32_t d = rec & 0xffffu;
+                        return ndist[d % kBanks] && first[d % kBanks] != d ? ndist[d % kBanks] : 0;
                     };
                     auto take = [&](uint32_t rec) {
-                        for (int r = 0; r < kPairs; ++r) {
-                            const uint32_t d = dword(rec, r);
-                            const size_t ix = static_cast<size_t>(r) * nbanks + d % nbanks;
-                            if (!ndist[ix]) { first[ix] = d; ndist[ix] = 1; }
-                            else if (first[ix] != d && ndist[ix] < 255) ++ndist[ix];
-                        }
+                        const uint32_t d = rec & 0xffffu, ix = d % kBanks;
+                        if (!ndist[ix]) { first[ix] = d; ndist[ix] = 1; }
+                        else if (first[ix] != d && ndist[ix] < 255) ++ndist[ix];
                         step[static_cast<size_t>(i) * kLanes + l] = rec;
                     };
                     auto& L_ = left[l];
@@ -851,7 +841,7 @@ void tmlib::bound_release(tm_library* L) {
 namespace {
 
 size_t image_bytes(const tm_library* L) {
-    return static_cast<size_t>(L->n_rows + 1) * L->bnd_L * sizeof(uint32_t);
+    return static_cast<size_t>(L->n_rows + 1) * L->bnd_L * sizeof(u32x2);
 }
 
 // Waves per workgroup: every wave slot when the image fills the LDS.
