@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace tmlib {
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
@@ -10,10 +12,23 @@ __device__ __forceinline__ int lane_id() { return __lane_id(); }
 // Uniform (scalar) copy of a wave-uniform value.
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
+// The wave's maximum (no NaN): along the rows of 16 lanes, then across them
+// (data-parallel moves of the vector unit; the LDS crossbar, which shuffles
+// go through, takes ten times as long per step), read from the last lane.
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m, 64));
-    return v;
+    auto step = [&](auto ctrl, auto rows) {
+        const int o = __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), ctrl.value,
+                                                  rows.value, 0xf, false);
+        v = fmaxf(v, __int_as_float(o));
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});    // row_shr:1
+    step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});    // row_shr:2
+    step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});    // row_shr:4
+    step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});    // row_shr:8
+    step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});    // row_bcast:15
+    step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});    // row_bcast:31
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
 __device__ __forceinline__ double wave_sum(double v) {

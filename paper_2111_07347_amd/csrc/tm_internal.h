@@ -96,12 +96,18 @@ struct SplitWork {
 // [B]) skips patterns whose entry is 0; compact: polar holds only the
 // library's touched rows, in order ([B, n_rows, n_theta]); split (optional)
 // runs the planned tasks instead of one workgroup per pattern (cand_count,
-// pat_mask and best_* unused). Enqueued on s.
+// pat_mask and best_* unused); may_allocate: a scan of all templates over a
+// small batch may take scratch for a split. Enqueued on s.
 int launch_match(const tm_library* lib, const float* polar, const double* norms, int32_t B,
                  int32_t N, int32_t* top_template, int32_t* top_angle, float* top_score,
                  float* best_score, int16_t* best_angle, const int32_t* cand, int32_t n_items,
                  const int32_t* cand_count, const int32_t* pat_mask, bool compact,
-                 hipStream_t s, const SplitWork* split = nullptr);
+                 hipStream_t s, const SplitWork* split = nullptr, bool may_allocate = false);
+
+// The N best of `parts` lists of N entries per pattern ([B, parts, N]).
+int merge_lists(const double* norms, int32_t B, int32_t parts, int32_t N, const int32_t* part_t,
+                const int32_t* part_s, const float* part_q, int32_t* top_template,
+                int32_t* top_angle, float* top_score, hipStream_t s);
 
 // Top-N over per-template scores [B, T] (tm_topn's kernel); best_angle may be
 // null (angles reported as 0). Enqueued on s.

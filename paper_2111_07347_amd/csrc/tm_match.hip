@@ -8,7 +8,8 @@
 // (k_i + s) mod n_theta] for all s. The kernel is bound by LDS reads and
 // VALU FMAs, not by HBM: each pattern is read once.
 //
-//   * One workgroup per pattern, 8 waves. The polar rows that the library
+//   * One workgroup per pattern, 8 waves (several for small batches, their
+//     lists merged by a kernel after it). The polar rows that the library
 //     touches are staged into LDS, each row followed by a wraparound halo, so
 //     column k_i + s needs no modulo.
 //   * Lanes are shifts: lane l, slot k holds C(l + 64 k); a spot costs one
@@ -48,6 +49,16 @@ namespace {
 constexpr int kWavesShared = 8;
 constexpr int kWavesWhole = 16;
 constexpr size_t kWholeCuLds = 80 * 1024;
+
+// Small batches: workgroups that share the patterns' groups, at least
+// kPartGroups groups per wave of each (twice that where a workgroup stages a
+// CU's whole LDS). One workgroup per pattern leaves CUs idle or with two waves
+// per SIMD, which wait for record loads. 200 patterns, 16 000 templates with
+// all scores written: 1570 us in 1 part, 820 in 3, 655 in 10, 663 in 16; 64
+// patterns, 600 templates: 84 us in 1 part, 68 in 6 (with the polar transform).
+constexpr int32_t kSplitGrid = 2048;
+constexpr int32_t kPartGroups = 2;
+constexpr int32_t kMaxParts = 16;
 
 // One union pixel of a group: LDS float offset within the band, then one
 // weight per group member.
@@ -173,8 +184,8 @@ __device__ __forceinline__ void accumulate_segments(const Rec<G>* __restrict__ r
 template <int K>
 __device__ __forceinline__ void finalize_slow(const float (&acc)[K], float mx, int t, int lane,
                                               float invP, int N, tmlib::TopState& st,
-                                              bool write_all, float* __restrict__ best_q,
-                                              short* __restrict__ best_s, size_t best_off) {
+                                              bool write_all,
+                                              float* __restrict__ best_q, short* __restrict__ best_s) {
     const float wm = tmlib::wave_max(mx);
     int s = 0;
     bool found = false;
@@ -188,8 +199,8 @@ __device__ __forceinline__ void finalize_slow(const float (&acc)[K], float mx, i
     }
     const float Q = wm * invP;
     if (write_all && lane == 0) {
-        best_q[best_off + t] = Q;
-        best_s[best_off + t] = static_cast<short>(s);
+        best_q[t] = Q;
+        best_s[t] = static_cast<short>(s);
     }
     if (tmlib::topn_beats(st, Q, t)) tmlib::topn_insert(st, Q, t, s, lane, N);
 }
@@ -267,7 +278,7 @@ match_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
         // per template). Tested on the bits, which the device build's
         // no-NaN assumption cannot fold away.
         if ((__double_as_longlong(pn) & 0x7ff0000000000000LL) == 0x7ff0000000000000LL) {
-            if (best_q)
+            if (best_q && lo == 0)
                 for (int t = threadIdx.x; t < Tp; t += NW * 64) {
                     best_q[static_cast<size_t>(b) * Tp + t] = __int_as_float(0x7fc00000);
                     best_s[static_cast<size_t>(b) * Tp + t] = -1;
@@ -280,7 +291,8 @@ match_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
             return;
         }
         const float invP = pn > 0.0 ? static_cast<float>(1.0 / pn) : 0.0f;
-        const size_t best_off = static_cast<size_t>(b) * Tp;
+        float* bq = best_q + static_cast<size_t>(b) * Tp;
+        short* bs = best_s + static_cast<size_t>(b) * Tp;
         tmlib::TopState st = tmlib::topn_init();
 
         if (n_bands == 1) {
@@ -354,8 +366,7 @@ match_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
                     if (t < 0) continue;
                     const float q = mx[m][g] * invP;
                     if (!write_all && !tmlib::ballot(tmlib::topn_beats(st, q, t))) continue;
-                    finalize_slow<K>(acc[m][g], mx[m][g], t, lane, invP, N, st, write_all,
-                                     best_q, best_s, best_off);
+                    finalize_slow<K>(acc[m][g], mx[m][g], t, lane, invP, N, st, write_all, bq, bs);
                 }
         }
 
@@ -369,8 +380,11 @@ match_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
         // cand_cnt[b] (optional) limits a candidate row to its first entries
         if (pat_mask && pat_mask[b] == 0) return;
         const int hi = (cand && cand_cnt) ? min(n_groups, max(0, cand_cnt[b])) : n_groups;
-        run(b, 0, hi, top_t + static_cast<size_t>(b) * N, top_s + static_cast<size_t>(b) * N,
-            top_q + static_cast<size_t>(b) * N);
+        // gridDim.y workgroups share a pattern's groups
+        const int p = blockIdx.y, np = gridDim.y;
+        const size_t o = (static_cast<size_t>(b) * np + p) * N;
+        run(b, static_cast<int>(static_cast<int64_t>(hi) * p / np),
+            static_cast<int>(static_cast<int64_t>(hi) * (p + 1) / np), top_t + o, top_s + o, top_q + o);
         return;
     }
     // split launch: claim tasks in order until none is left (every workgroup
@@ -450,7 +464,7 @@ int tmlib::launch_match(const tm_library* lib, const float* polar, const double*
                         int32_t N, int32_t* top_template, int32_t* top_angle, float* top_score,
                         float* best_score, int16_t* best_angle, const int32_t* cand,
                         int32_t n_items, const int32_t* cand_count, const int32_t* pat_mask,
-                        bool compact, hipStream_t s, const tmlib::SplitWork* split) {
+                        bool compact, hipStream_t s, const tmlib::SplitWork* split, bool may_allocate) {
     const int K = tmlib::slots_for(lib->n_theta);
     const bool multi = lib->n_bands > 1;
     const int G = cand ? 1 : lib->group;
@@ -467,14 +481,37 @@ int tmlib::launch_match(const tm_library* lib, const float* polar, const double*
     const int32_t* seg = cand ? lib->seg_single() : lib->d_seg;
     const int32_t n_groups = cand ? n_items : lib->n_groups;
     const tmlib::SplitWork work = split ? *split : tmlib::SplitWork{};
-    hipLaunchKernelGGL(fn, dim3(split ? split->grid : B), dim3(nw * 64), lds_bytes, s, polar, norms,
+    int32_t parts = 1;
+    if (may_allocate && !cand && !split && !pat_mask)
+        parts = std::max(1, std::min({kSplitGrid / B, n_groups / (kPartGroups * nw * (nw == kWavesWhole ? 2 : 1)), kMaxParts}));
+    tmlib::Scratch mem;
+    int32_t *out_t = top_template, *out_s = top_angle;
+    float* out_q = top_score;
+    if (parts > 1) {
+        const size_t rows = static_cast<size_t>(B) * parts * N;
+        mem.add(out_t, rows);
+        mem.add(out_s, rows);
+        mem.add(out_q, rows);
+        if (mem.allocate(s) != TM_OK) {
+            (void)hipGetLastError();             // no scratch: one workgroup per pattern needs none
+            tmlib::clear_error();
+            parts = 1;
+            out_t = top_template;
+            out_s = top_angle;
+            out_q = top_score;
+        }
+    }
+    hipLaunchKernelGGL(fn, split ? dim3(split->grid) : dim3(B, parts), dim3(nw * 64), lds_bytes, s, polar, norms,
                        compact ? lib->n_rows : lib->R, lib->n_theta,
                        compact ? nullptr : lib->d_rows, lib->d_band_off, lib->n_bands, lib->row_width,
-                       recs, seg, lib->d_members, n_groups, lib->Tp, N, top_template, top_angle,
-                       top_score, best_score, reinterpret_cast<short*>(best_angle), cand,
+                       recs, seg, lib->d_members, n_groups, lib->Tp, N, out_t, out_s,
+                       out_q, best_score, reinterpret_cast<short*>(best_angle), cand,
                        cand_count, pat_mask, work);
-    TM_HIP(hipGetLastError());
-    return TM_OK;
+    const hipError_t e = hipGetLastError();
+    int r = e == hipSuccess ? TM_OK : tmlib::hip_fail(e, "match kernel launch");
+    if (parts == 1) return r;
+    if (!r) r = tmlib::merge_lists(norms, B, parts, N, out_t, out_s, out_q, top_template, top_angle, top_score, s);
+    return mem.release(s, r);
 }
 
 // tm_match_batch and its variant without allocations: scratch == nullptr
@@ -590,7 +627,7 @@ int tmlib::match_batch_impl(const tm_library* lib, const float* polar, const dou
                                         compact, s)
                     : tmlib::launch_match(lib, polar, norms, B, N, top_template, top_angle, top_score,
                                           best_score, best_angle, nullptr, 0, nullptr, nullptr, compact,
-                                          s);
+                                          s, nullptr, may_allocate);
         if (!r && n_rescored) r = tmlib::fill_i32(n_rescored, B, lib->Tp, s);
         return r;
     }

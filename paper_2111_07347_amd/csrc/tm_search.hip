@@ -1054,6 +1054,7 @@ search_kernel(const SearchArgs a) {
 
 // The parts' lists of a split search merged into the pattern's rows, one
 // wave per pattern (score descending, ties to the lower template index).
+// give, full: optional.
 __global__ void __launch_bounds__(256)
 merge_parts(const double* __restrict__ norms, int B, int parts, int N,
             const int* __restrict__ pt, const int* __restrict__ ps, const float* __restrict__ pq,
@@ -1064,8 +1065,8 @@ merge_parts(const double* __restrict__ norms, int B, int parts, int N,
     if (b >= B) return;
     const size_t e0 = static_cast<size_t>(b) * parts * N, o = static_cast<size_t>(b) * N;
     // given up by any part: by all (the plain scan writes the rows)
-    const bool any = tmlib::ballot(lane < parts && give[b * parts + lane] != 0) != 0;
-    if (lane == 0) full[b] = any ? 1 : 0;
+    const bool any = give && tmlib::ballot(lane < parts && give[b * parts + lane] != 0) != 0;
+    if (full && lane == 0) full[b] = any ? 1 : 0;
     if (any) return;
     const double pn = norms[b];
     if ((__double_as_longlong(pn) & 0x7ff0000000000000LL) == 0x7ff0000000000000LL) {
@@ -1421,6 +1422,15 @@ SearchArgs pattern_args(const tm_library* lib, const float* polar, const double*
 }
 
 }  // namespace
+
+int tmlib::merge_lists(const double* norms, int32_t B, int32_t parts, int32_t N, const int32_t* part_t,
+                       const int32_t* part_s, const float* part_q, int32_t* top_template,
+                       int32_t* top_angle, float* top_score, hipStream_t s) {
+    hipLaunchKernelGGL(merge_parts, dim3((B + 3) / 4), dim3(256), 0, s, norms, B, parts, N, part_t, part_s,
+                       part_q, nullptr, nullptr, top_template, top_angle, top_score);
+    TM_HIP(hipGetLastError());
+    return TM_OK;
+}
 
 int tmlib::refine_search(const tm_library* lib, const float* polar, const double* norms, int32_t B,
                          int32_t N, const float* amax, const float* Qc, int32_t n_cs,

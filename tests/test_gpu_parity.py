@@ -441,3 +441,32 @@ def test_nonfinite_pattern_is_flagged_and_nan_options_rejected(tm, c1, c1_lib):
         assert r == tm.TM_EINVAL, field
         assert "outside [0, 1]" in tm.last_error()
     lib.free()
+
+
+@pytest.mark.parametrize("B,n", [(1, 300), (3, 13), (300, 300), (2, 1)])
+def test_match_split_over_workgroups(tm, c1, c1_lib, B, n):
+    """Scans of few patterns are split over workgroups, whose lists are
+    merged; none of it may show: the rows and every template's score and angle
+    are those of the allocation-free scan, which never splits."""
+    import torch
+    _say("match split", B, n)
+    off = c1_lib["offsets"][:n + 1]
+    m = int(off[-1])
+    grid = _grid_for(tm, c1)
+    lib = tm.Library(c1_lib["kx"][:m], c1_lib["ky"][:m], c1_lib["intensity"][:m], off,
+                     synth.px_per_inv_A(c1), grid, mirror=True)
+    imgs = synth.make_patterns(c1, c1_lib, [i % 300 for i in range(B)])
+    imgs[-1, 0, 0] = np.nan if B == 3 else imgs[-1, 0, 0]
+    polar, norms, _ = tm.polar_transform(torch.from_numpy(np.ascontiguousarray(imgs)).cuda(), grid)
+    if B == 3:
+        norms[-1] = float("nan")
+    N = min(5, 2 * n)
+    got = [o.cpu().numpy() for o in tm.match_batch(lib, polar, norms, N, with_best=True)]
+    out = [torch.empty(o.shape, dtype=dt, device="cuda")
+           for o, dt in zip(got, (torch.int32, torch.int32, torch.float32, torch.float32, torch.int16))]
+    r = tm._lib.tm_match_batch_static(lib._h, polar.data_ptr(), norms.data_ptr(), None, B, None, N,
+                                      *[o.data_ptr() for o in out], None)
+    assert r == tm.TM_OK
+    want = [o.cpu().numpy() for o in out]
+    for g, w in zip(got, want):
+        assert np.array_equal(g, w, equal_nan=g.dtype.kind == "f")
