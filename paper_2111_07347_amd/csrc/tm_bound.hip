@@ -113,13 +113,25 @@ constexpr int kBuildWaves = 8;             // waves that build the window image'
 constexpr int kParts = 1024;               // chunk ranges (waves x workgroups of a pattern)
 constexpr int64_t kSearchRecords = 8192;   // records of a plain scan from which the search pays
 constexpr int64_t kSearchWork = 3000000;   //   for a sparse library, whatever the batch (records x
-constexpr int64_t kBoundRecords = 65536;   //   patterns otherwise), and for the others
+constexpr int64_t kBoundRecords = 131072;  //   patterns otherwise), and for the others (766 ortho-
+                                           //   rhombic templates, 483 patterns: 1.8 ms scanned, 2.1
+                                           //   searched; 999, 52 patterns, 720 columns: 1.0 and 2.2;
+                                           //   3000, 512 patterns: 0.9 searched)
 constexpr int32_t kSearchChunk = 65536;    // patterns of a plain path's search at a time, and
 constexpr size_t kSearchScratch = size_t(4) << 30;   // the bytes of their bounds
 constexpr int kFillGrid = 512;             // workgroups that fill the chip (two per CU)
 constexpr int kRefineBatch = 128;          // largest batch of a dense library that is refined,
 constexpr int kRefineTemplates = 8192;     //   its least templates
 constexpr int64_t kRefineSpots = 24;       //   and pixels per template
+// Columns of a polar row: with up to two per lane a scan of a dense library is
+// as cheap as its bounds (7933 orthorhombic templates, 90 columns, 10 patterns:
+// 0.35 ms scanned, 0.84 searched); beyond six, patterns without a clear best
+// template cost the refinement more than the certified rescoring (13 908
+// templates, 720 columns, 2 patterns: 3.3 against 2.2 ms).
+constexpr int kRefineColumns[2] = {128, 384};
+constexpr int kFewColumns = 192;           // few columns, many pixels per template, many
+constexpr int64_t kManySpots = 10;         //   patterns (see searches_all)
+constexpr int32_t kManyPatterns = 512;
 constexpr int kMaxSplit = 32;              // workgroups per pattern of a small batch
 constexpr int kMaxCols = 12;               // window columns per lane (n_theta <= 768)
 
@@ -858,6 +870,23 @@ int bound_split(const tm_library* L, int32_t B) {
     return split;
 }
 
+// Whether a sparse library's search bounds all its templates in the search's
+// own windows (tm_search.hip). With 13 pixels per template (HCP) it does not
+// pay on few columns, where the windows are narrow, 12 to 24 columns, and the
+// scan of survivors that follows the wide ones costs less (180 columns, 2000 to
+// 6300 templates, 1024 patterns: 499 to 1054 us searched, 425 to 990
+// certified; 360 columns: 460 to 961 against 507 to 1151; FCC, 7 pixels, 180
+// columns: 433 to 1107 against 453 to 1083), except for a few patterns, which
+// cannot fill the chip with its passes (21 of them, 3897 templates: 238
+// against 455 us); nor on more than six columns per lane (720 columns, 1000 to
+// 8000 templates, 8 and 32 patterns: 186 to 540 us against 137 to 506; FCC:
+// 118 to 331 against 257 to 467).
+bool searches_all(const tm_library* L, int32_t B) {
+    const bool many = L->n_spots >= kManySpots * L->Tp;
+    const bool few_columns = L->n_theta <= kFewColumns && B >= kManyPatterns;
+    return L->sr_all && !(many && (few_columns || L->n_theta > kRefineColumns[1]));
+}
+
 }  // namespace
 
 int tmlib::bound_scores_impl(const tm_library* L, const float* polar, const double* norms,
@@ -915,11 +944,12 @@ int tmlib::bound_match(const tm_library* lib, const float* polar, const double* 
                        int32_t* top_angle, float* top_score, bool compact, hipStream_t s) {
     const int Tp = lib->Tp;
     const int n_cs = lib->bnd_chunks * kLanes;
-    if (lib->sr_all && !n_rescored)
+    if (!n_rescored && searches_all(lib, B))
         return tmlib::search_all(lib, polar, norms, B, N, top_template, top_angle, top_score, compact, s);
     // the certified rescoring's list holds one workgroup's lanes
     const bool refine = lib->search && !n_rescored && B <= kRefineBatch && Tp >= kRefineTemplates &&
-                        lib->n_spots >= kRefineSpots * Tp;
+                        lib->n_spots >= kRefineSpots * Tp &&
+                        lib->n_theta > kRefineColumns[0] && lib->n_theta <= kRefineColumns[1];
     const int split = refine ? bound_split(lib, B) : 1;
     const int n_list = split * bound_waves(lib) * 64;
     const size_t nl = static_cast<size_t>(B) * n_list;
@@ -956,14 +986,14 @@ int tmlib::bound_match(const tm_library* lib, const float* polar, const double* 
 bool tmlib::search_pays(const tm_library* lib, int32_t B) {
     if (lib->sr_all)
         return lib->n_records >= kSearchRecords || static_cast<int64_t>(B) * lib->n_records >= kSearchWork;
-    return lib->bound && lib->n_records >= kBoundRecords;
+    return lib->bound && lib->n_records >= kBoundRecords && lib->n_theta > kRefineColumns[0];
 }
 
 int tmlib::search_top(const tm_library* lib, const float* polar, const double* norms, int32_t B,
                       int32_t N, int32_t* top_template, int32_t* top_angle, float* top_score,
                       bool compact, hipStream_t s) {
     const size_t row = static_cast<size_t>(lib->bnd_chunks) * kLanes * sizeof(float);
-    const int32_t chunk = lib->sr_all ? kSearchChunk
+    const int32_t chunk = searches_all(lib, B) ? kSearchChunk
                                       : static_cast<int32_t>(std::max<size_t>(1, std::min<size_t>(kSearchChunk, kSearchScratch / row)));
     const size_t pattern = static_cast<size_t>(compact ? lib->n_rows : lib->R) * lib->n_theta;
     for (int32_t b0 = 0; b0 < B; b0 += chunk) {

@@ -56,9 +56,20 @@ constexpr size_t kWholeCuLds = 80 * 1024;
 // per SIMD, which wait for record loads. 200 patterns, 16 000 templates with
 // all scores written: 1570 us in 1 part, 820 in 3, 655 in 10, 663 in 16; 64
 // patterns, 600 templates: 84 us in 1 part, 68 in 6 (with the polar transform).
+// What the split and its merge cost (10 us) is saved from kSplitWork vector
+// instructions of a scan on: 198 FCC templates on 157 columns, 2e4 of them, take
+// 56 us whole and 65 split, 300 on 360 columns, 5e4, 84 and 68. Where the rows
+// fill a CU's LDS the patterns alone fill the chip sooner: 483 patterns,
+// 766 orthorhombic templates, 1.84 ms whole and 2.13 in four parts.
 constexpr int32_t kSplitGrid = 2048;
+constexpr int32_t kSplitWhole = 512;
+constexpr int64_t kSplitWork = 32768;
 constexpr int32_t kPartGroups = 2;
 constexpr int32_t kMaxParts = 16;
+
+// Records x patterns of a plain scan below which the Fourier route's dozen
+// launches do not pay.
+constexpr int64_t kScanWork = 1500000;
 
 // One union pixel of a group: LDS float offset within the band, then one
 // weight per group member.
@@ -482,8 +493,10 @@ int tmlib::launch_match(const tm_library* lib, const float* polar, const double*
     const int32_t n_groups = cand ? n_items : lib->n_groups;
     const tmlib::SplitWork work = split ? *split : tmlib::SplitWork{};
     int32_t parts = 1;
-    if (may_allocate && !cand && !split && !pat_mask)
-        parts = std::max(1, std::min({kSplitGrid / B, n_groups / (kPartGroups * nw * (nw == kWavesWhole ? 2 : 1)), kMaxParts}));
+    if (may_allocate && !cand && !split && !pat_mask && lib->n_records * (1 + G * K) >= kSplitWork) {
+        const int whole = nw == kWavesWhole;
+        parts = std::max(1, std::min({(whole ? kSplitWhole : kSplitGrid) / B, n_groups / (kPartGroups * nw * (1 + whole)), kMaxParts}));
+    }
     tmlib::Scratch mem;
     int32_t *out_t = top_template, *out_s = top_angle;
     float* out_q = top_score;
@@ -608,17 +621,28 @@ int tmlib::match_batch_impl(const tm_library* lib, const float* polar, const dou
     }
     if (int r = tmlib::require_device()) return r;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    // Scratch may be taken by the searches below not in the allocation-free
+    // entry, nor while the stream is captured (the plain scan needs none)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (!scratch && s) TM_HIP(hipStreamIsCapturing(s, &capture));
+    const bool may_allocate = !scratch && capture == hipStreamCaptureStatusNone;
+    // Certified rescoring makes the Fourier route's rows those of the plain
+    // path, whatever the spectra say; unless the caller asks for the number
+    // of certified templates, the plain path gives them sooner where its
+    // search with bounds pays (8000 HCP templates: 512 patterns 4979 ->
+    // 553 us, 8 of them at half the size 534 -> 220; 3000 orthorhombic ones:
+    // 512 patterns 2741 -> 898, 4 of them 489 -> 231) or the scan is small
+    // (300 FCC templates, 64 patterns: 212 -> 59 us; 100 orthorhombic ones,
+    // 300 patterns, 2e6 records: 218 -> 224, beyond the rule).
+    if (coarse == TM_COARSE_FFT && policy == TM_RESCORE_CERTIFIED && !n_rescored && may_allocate &&
+        (tmlib::search_pays(lib, B) || static_cast<int64_t>(B) * lib->n_records < kScanWork))
+        coarse = TM_COARSE_NONE;
     if (coarse == TM_COARSE_FFT)
         return tmlib::fft_match(lib, polar, norms, B, N, policy, rescore_keep, n_rescored,
                                 top_template, top_angle, top_score, compact, s);
     if (coarse == TM_COARSE_BOUND)
         return tmlib::bound_match(lib, polar, norms, B, N, rescore_keep, n_rescored, top_template,
                                   top_angle, top_score, compact, s);
-    // Scratch may be taken here (not in the allocation-free entry, nor while
-    // the stream is captured: the plain scan needs none)
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (!scratch && s) TM_HIP(hipStreamIsCapturing(s, &capture));
-    const bool may_allocate = !scratch && capture == hipStreamCaptureStatusNone;
     if (n_keep == 0) {
         // Without per-template outputs only the N best matter: the same rows
         // come from the search with bounds (tm_bound.hip, tm_search.hip)

@@ -256,3 +256,22 @@ def test_compact_rows_equal_full(tm, c1, c1_lib):
     comp = tm.match_batch(lib, cpolar, cnorms, 5, coarse="fft")
     for u, v in zip(full, comp):
         assert torch.equal(u, v)
+
+
+@pytest.mark.parametrize("B,n", [(64, 300), (2, 300), (700, 300), (3, 9)])
+def test_certified_rows_whichever_way_they_come(tm, c1, c1_lib, B, n):
+    """A call that asks for the certified sets runs the Fourier kernels; one
+    that does not may take the plain path (small scans, and where its search
+    pays). The rows are the same bits."""
+    import torch
+    off = c1_lib["offsets"][:n + 1]
+    m = int(off[-1])
+    part = dict(kx=c1_lib["kx"][:m], ky=c1_lib["ky"][:m], intensity=c1_lib["intensity"][:m], offsets=off)
+    lib, grid = _lib(tm, part, c1, synth.px_per_inv_A(c1))
+    _say("certified rows", B, n)
+    polar, norms, _ = _polar(tm, synth.make_patterns(c1, c1_lib, [i % 300 for i in range(B)]), grid)
+    nr = torch.zeros(B, dtype=torch.int32, device="cuda")
+    want = tm.match_batch(lib, polar, norms, 5, coarse="fft", n_rescored=nr)
+    assert int(nr.min()) > 0
+    got = tm.match_batch(lib, polar, norms, 5, coarse="fft")
+    assert all(torch.equal(g, w) for g, w in zip(got, want))
