@@ -552,7 +552,7 @@ int split_pass(const tm_library* lib, const float* polar, const double* norms, i
                float* top_score, bool compact, hipStream_t s) {
     // workgroups for the tasks, as many as the chip holds (their LDS: the
     // band's rows)
-    const int chunk = want_full ? chunk_full(lib) : kChunkCand;
+    const int chunk = cand ? kChunkCand : chunk_full(lib);
     const size_t lds = staged_bytes(lib);
     const int64_t fit = 256 * std::min<int64_t>(8, std::max<int64_t>(1, static_cast<int64_t>(160 * 1024 / lds)));
     const int grid = static_cast<int>(std::max<int64_t>(1, std::min({most_tasks(B, n_items, chunk), fit,
@@ -668,12 +668,13 @@ int tmlib::certified_rescore(const tm_library* lib, const float* polar, const do
 
 int tmlib::full_scans(const tm_library* lib, const float* polar, const double* norms, int32_t B,
                       int32_t N, const int32_t* full, int32_t* top_template, int32_t* top_angle,
-                      float* top_score, bool compact, hipStream_t s) {
+                      float* top_score, bool compact, hipStream_t s, const int32_t* cand, int32_t n_cand) {
+    const int32_t n_items = cand ? n_cand : lib->n_groups;
     tmlib::Scratch mem;
-    SplitScratch sc(mem, B, N, most_tasks(B, lib->n_groups, chunk_full(lib)));
+    SplitScratch sc(mem, B, N, most_tasks(B, n_items, cand ? kChunkCand : chunk_full(lib)));
     int r = mem.allocate(s);
     if (!r)
-        r = split_pass(lib, polar, norms, B, N, full, true, nullptr, nullptr, lib->n_groups, sc,
+        r = split_pass(lib, polar, norms, B, N, full, true, cand, nullptr, n_items, sc,
                        top_template, top_angle, top_score, compact, s);
     return mem.release(s, r);
 }

@@ -161,10 +161,12 @@ int certified_rescore(const tm_library* lib, const float* polar, const double* n
                       const int32_t* first_col = nullptr, int32_t n_list = 0);
 
 // Plain scans of the patterns with full[b] != 0 into their output rows, each
-// spread over many workgroups (tm_certify.hip). Enqueued on s.
+// spread over many workgroups (tm_certify.hip): of all templates, or of the
+// candidates cand [B, n_cand]. Enqueued on s.
 int full_scans(const tm_library* lib, const float* polar, const double* norms, int32_t B,
                int32_t N, const int32_t* full, int32_t* top_template, int32_t* top_angle,
-               float* top_score, bool compact, hipStream_t s);
+               float* top_score, bool compact, hipStream_t s, const int32_t* cand = nullptr,
+               int32_t n_cand = 0);
 
 // Window upper bounds (tm_bound.hip): library data built at load (only when
 // every template weight is non-negative and the window image fits the LDS

@@ -669,11 +669,20 @@ int tmlib::match_batch_impl(const tm_library* lib, const float* polar, const dou
     int r = tmlib::prefilter_kept(lib, profiles, B, n_keep, prec, items, n_items, mirror, s, S);
     // of the kept templates, too, only the N best matter
     const bool search = may_allocate && tmlib::search_items_pays(lib, n_items);
-    if (!r)
-        r = search ? tmlib::search_items(lib, polar, norms, B, N, items, n_items, top_template, top_angle,
-                                         top_score, compact, s)
-                   : tmlib::launch_match(lib, polar, norms, B, N, top_template, top_angle, top_score,
-                                         nullptr, nullptr, items, n_items, nullptr, nullptr, compact, s);
+    bool scan = !search;
+    if (!r && search) {
+        r = tmlib::search_items(lib, polar, norms, B, N, items, n_items, top_template, top_angle,
+                                top_score, compact, s);
+        if (r == TM_ENOMEM) {
+            (void)hipGetLastError();             // no scratch: the scan of the lists needs none
+            tmlib::clear_error();
+            r = TM_OK;
+            scan = true;
+        }
+    }
+    if (!r && scan)
+        r = tmlib::launch_match(lib, polar, norms, B, N, top_template, top_angle, top_score,
+                                nullptr, nullptr, items, n_items, nullptr, nullptr, compact, s);
     if (!r && n_rescored) r = tmlib::fill_i32(n_rescored, B, n_items, s);
     if (!scratch) {
         hipError_t e = hipFreeAsync(items, s);

@@ -73,8 +73,8 @@ constexpr int kPend = 32;                // columns of Qc per wave and round
 constexpr int kSel = 256;                // listed columns per round (kAll, kItems)
 constexpr uint32_t kDone = 0xffffu;      // a bound that is dealt with
 constexpr double kSparse = 24;           // most records per template of a sparse library
-constexpr int kItemsSparse = 512;        // listed templates from which a search pays: sparse
-constexpr int kItemsDense = 2048;        //   and dense libraries
+constexpr double kItemsSparse = 150000;  // a list's pixels x shift slots from which a search pays:
+constexpr double kItemsDense = 450000;   //   sparse and dense libraries (see search_items_pays)
 constexpr int kAllTemplates = 32768;     // most templates bounded in the workgroup (2 bytes each)
 constexpr int kAllSteps = 8192;          // and most steps of 64 records for that
 constexpr int kBuildWaves = 8;           // waves that build the image (row buffers share the lists' LDS)
@@ -1402,11 +1402,8 @@ int run_search(const tm_library* lib, Kind kind, SearchArgs a, int32_t B, size_t
     }
     // patterns given up: their items scored one and all
     if (!r)
-        r = kind == kItems ? tmlib::launch_match(lib, a.polar, a.norms, B, a.N, top_template, top_angle,
-                                                 top_score, nullptr, nullptr, a.items, a.n_items, nullptr,
-                                                 full, !a.rows, s)
-                           : tmlib::full_scans(lib, a.polar, a.norms, B, a.N, full, top_template, top_angle,
-                                               top_score, !a.rows, s);
+        r = tmlib::full_scans(lib, a.polar, a.norms, B, a.N, full, top_template, top_angle, top_score,
+                              !a.rows, s, kind == kItems ? a.items : nullptr, a.n_items);
     return mem.release(s, r);
 }
 
@@ -1456,9 +1453,14 @@ int tmlib::search_all(const tm_library* lib, const float* polar, const double* n
                       top_angle, top_score, s);
 }
 
+// By the work of the scan of a list that the search replaces. Measured (scan,
+// search; us): FCC 84 000 at 256 patterns 467, 519 and at 2048 1562, 1502,
+// 168 000 at 256 818, 713; HCP 62 400 279, 421, 124 800 454, 502, 249 600 at 64
+// 801, 589; orthorhombic 456 000 1290, 1303, 1.0e6 at 64 1313, 538.
 bool tmlib::search_items_pays(const tm_library* lib, int32_t n_items) {
     const bool sparse = static_cast<double>(lib->n_spots) <= kSparse * lib->Tp;
-    return lib->search && n_items >= (sparse ? kItemsSparse : kItemsDense) && n_items <= kAllTemplates &&
+    const double work = static_cast<double>(lib->n_spots) / lib->Tp * n_items * tmlib::slots_for(lib->n_theta);
+    return lib->search && work >= (sparse ? kItemsSparse : kItemsDense) && n_items <= kAllTemplates &&
            lds_bytes<kItems, 16>(lib) + 2 * static_cast<size_t>(n_items) + 256 <= kMaxLds;
 }
 
