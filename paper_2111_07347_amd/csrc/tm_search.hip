@@ -1335,7 +1335,7 @@ int run_search(const tm_library* lib, Kind kind, SearchArgs a, int32_t B, size_t
     a.top_q = top_score;
     // A plain scan takes about records x (1 + group x slots) wave
     // instructions, a window of a candidate kWindowCost per record and
-    // kWindowMore: a part gives up when it has spent a quarter of its share of
+    // kWindowMore: a part gives up when it has spent half of its share of
     // the scan, at the latest after kMaxGive windows (a batch waits for its
     // last workgroup: a large one, or one with long scans, less so).
     const double mean = static_cast<double>(lib->n_spots) / lib->Tp;
@@ -1344,7 +1344,7 @@ int run_search(const tm_library* lib, Kind kind, SearchArgs a, int32_t B, size_t
     const double scan = kind == kItems ? a.n_items * mean * (2 + 2 * slots)
                                        : static_cast<double>(lib->n_records) * (1 + lib->group * slots);
     const double most = std::max<double>({kMaxGive, B / 8.0, scan / (64 * window)});
-    a.give_up = static_cast<int>(std::min(most, std::max<double>(kMinGive, scan / (4 * window * parts))));
+    a.give_up = static_cast<int>(std::min(most, std::max<double>(kMinGive, scan / (2 * window * parts))));
     // scratch: the parts' lists, flags of given-up parts and patterns
     const size_t ne = static_cast<size_t>(B) * parts * a.N;
     int32_t* full;
