@@ -666,7 +666,9 @@ int tm_fft_scores(const tm_library* lib, const float* polar, const double* norms
  *   polar, norms  as in tm_match_batch; compact_rows as in tm_fft_scores.
  *   B             >= 0 (0 is a no-op).
  *   bound_out     device, [B, T'] float32, written. A pattern with a
- *                 non-finite norm gets 0 (tm_match_batch flags it).
+ *                 non-finite norm gets 0 (tm_match_batch flags it); one whose
+ *                 largest |P| over the touched rows is below 2^-100, or whose
+ *                 1 / ||P|| is past float32, gets +infinity.
  * Errors: TM_EINVAL, TM_EUNSUPPORTED, TM_EHIP, TM_ENODEV. */
 int tm_bound_scores(const tm_library* lib, const float* polar, const double* norms, int32_t B,
                     int32_t compact_rows, float* bound_out, void* hip_stream);

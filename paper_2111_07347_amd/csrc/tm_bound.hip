@@ -37,7 +37,8 @@
 //   Q^_t = (U_t / (scale 2^10)) / (1 - gamma_{nmax + 1}) / ||P|| * (1 + 2^-19),
 //
 // rounded up, which is at least the plain path's float32 Q_t of every
-// template.
+// template. A pattern that is too faint for these scales (tm_window.h) gets
+// infinite bounds: every template is scored.
 //
 // Quarter-turn pairing. A pixel at column k = q win + r (q = 0..3, r <
 // win) needs M at r + (q + S) win for S = 0..3, the 4 maxima M[r + i win],
@@ -97,16 +98,20 @@
 
 #include "tm_device.h"
 #include "tm_internal.h"
+#include "tm_window.h"
 
 namespace {
+
+using tmlib::f16_up;
+using tmlib::gamma32;
+using tmlib::h2f;
+using tmlib::kWeightExp;
 
 constexpr int kShifts = 4;                 // coarse shifts per template
 constexpr int kLanes = 64;                 // templates per chunk, one per lane
 constexpr int kUnitSteps = 4;              // records per lane and unit (one 16-byte load)
 constexpr int kBanks = 32;                 // LDS banks of 8 bytes, per half-wave
 constexpr int kChoices = 64;               // records tried per lane and step
-constexpr int kWeightExp = 10;             // float16 weights carry w * 2^10
-constexpr int kImageExp = 14;              // window maxima scaled below 2^14
 constexpr size_t kLdsBudget = 128 * 1024;  // window image (16-bit offsets)
 constexpr int kFirst = 48;                 // best bounds scored exactly first
 constexpr int kBuildWaves = 8;             // waves that build the window image's rows
@@ -137,20 +142,6 @@ constexpr int kMaxCols = 12;               // window columns per lane (n_theta <
 
 // ---------------------------------------------------------------- host side
 
-double gamma32(double n) {
-    const double u = std::ldexp(1.0, -24);
-    return n * u / (1.0 - n * u);
-}
-
-// float16 bits of the smallest float16 >= x (0 <= x < 65504).
-uint16_t half_up(float x) {
-    const _Float16 h = static_cast<_Float16>(x);
-    uint16_t b;
-    std::memcpy(&b, &h, 2);
-    if (static_cast<float>(h) < x) ++b;
-    return b;
-}
-
 // Per-wave LDS scratch of the window-image build, in halves: a row of n
 // columns plus a halo of wlen + o, and its block maxima (blocks of o).
 size_t scratch_halves(int n, int win) {
@@ -167,18 +158,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) const uint16_t lds_u16;
 typedef __attribute__((address_space(3))) const u32x2 lds_u32x2;
-
-__device__ __forceinline__ float h2f(uint32_t bits16) {
-    return static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(bits16)));
-}
-
-// float16 bits of the smallest float16 >= x (0 <= x <= 2^14).
-__device__ __forceinline__ uint16_t f16_up(float x) {
-    const _Float16 h = static_cast<_Float16>(x);
-    uint16_t b = __builtin_bit_cast(uint16_t, h);
-    if (static_cast<float>(h) < x) ++b;
-    return b;
-}
 
 // LDS byte address of a record's entry: the record's 16-bit entry number
 // times 8 plus the image base, in one multiply-add of the low 16 bits
@@ -220,7 +199,7 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
              const int* __restrict__ rows, const int* __restrict__ rowat, int n_rows, int Lrow,
              int win, int wlen, int scr_stride,
              const u32x4* __restrict__ recs, int rec_bytes, const int* __restrict__ chunk_end,
-             const int4* __restrict__ slot_end, const int* __restrict__ part, int n_cs,
+             const int4* __restrict__ slot_end, const int* __restrict__ part, int n_cs, int Tp,
              float dfac, float* __restrict__ Qc,
              float* __restrict__ lane_q, int32_t* __restrict__ lane_c, float* __restrict__ amax) {
     extern __shared__ uint16_t m16[];        // window image: pairs of halves
@@ -273,9 +252,20 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
 #pragma unroll
     for (int w = 1; w < NW; ++w) A = fmaxf(A, red[w]);
     if (amax && blockIdx.y == 0 && threadIdx.x == 0) amax[b] = A;
-    int e = 0;
-    (void)frexpf(A, &e);                        // A = m 2^e, m in [0.5, 1)
-    const float scale = A > 0.0f ? ldexpf(1.0f, kImageExp - e) : 1.0f;
+    const float invP = tmlib::inverse_up(pn);
+    // no bounds at this scale: infinite ones, which rule out no template
+    if (tmlib::no_window_bounds(A, invP)) {
+        if (blockIdx.y == 0)
+            for (int i = threadIdx.x; i < n_cs; i += NW * 64) qrow[i] = i < Tp ? INFINITY : 0.0f;
+        if (lane_q) {
+            const int i = static_cast<int>(blockIdx.y) * NW * 64 + threadIdx.x;
+            lane_q[lists + threadIdx.x] = i < Tp ? INFINITY : -INFINITY;
+            lane_c[lists + threadIdx.x] = i < Tp ? i : -1;
+        }
+        return;
+    }
+    const tmlib::WindowScale ws = tmlib::window_scale(A);
+    const float scale = ws.image;
     // 2. window maxima. Rounding up to float16 is monotone, so the maximum
     // of the rounded values is the rounded maximum: each row goes once, as
     // clamped (at 0), scaled, rounded-up float16 bits, into the wave's row
@@ -382,13 +372,7 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
     // = 1 / (scale 2^10) a power of 2, invP = 1 / ||P|| rounded up (every
     // operand non-negative; the three roundings are more than restored by
     // the last factor)
-    float invP = 0.0f;
-    if (pn > 0.0) {
-        const double ip = 1.0 / pn;
-        invP = static_cast<float>(ip);
-        if (static_cast<double>(invP) < ip) invP = nextafterf(invP, INFINITY);
-    }
-    const float out_scale = 1.0f / (scale * static_cast<float>(1 << kWeightExp));   // power of 2
+    const float out_scale = ws.undo;            // 1 / (scale 2^10), a power of 2
     const uint32_t base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u16*)m16));
     // the wave's chunks [c_begin, c_end) hold about 1 / (NW gridDim.y) of
     // the units
@@ -595,7 +579,7 @@ int tmlib::bound_prepare(tm_library* L, const std::vector<std::vector<HostPixel>
             // places in the image below
             const uint32_t off = static_cast<uint32_t>(row_index[p.j]) * Lrow +
                                  static_cast<uint32_t>(k - q * win);
-            const uint32_t w16 = half_up(std::ldexp(w32, kWeightExp));
+            const uint32_t w16 = f16_up(std::ldexp(w32, kWeightExp));
             qv[q].push_back(off | (w16 << 16));
         }
         const int cnt = static_cast<int>(pix[t].size());
@@ -603,7 +587,7 @@ int tmlib::bound_prepare(tm_library* L, const std::vector<std::vector<HostPixel>
         // the margin record: weight c_t 2^10 (rounded up), value A (one
         // place for all: a broadcast read)
         const double cf = gamma32(cnt) * wsum * (1.0 + 0x1p-20);
-        const uint32_t c16 = half_up(static_cast<float>(std::ldexp(cf, kWeightExp) * (1.0 + 0x1p-20)));
+        const uint32_t c16 = f16_up(static_cast<float>(std::ldexp(cf, kWeightExp) * (1.0 + 0x1p-20)));
         int qs = 0;
         for (int q = 1; q < kShifts; ++q)
             if (qv[q].size() < qv[qs].size()) qs = q;
@@ -915,7 +899,7 @@ int tmlib::bound_scores_impl(const tm_library* L, const float* polar, const doub
                            reinterpret_cast<const u32x4*>(L->d_bnd_recs),
                            static_cast<int>(L->bnd_units * 1024), L->d_bnd_end,
                            reinterpret_cast<const int4*>(L->d_bnd_slots),
-                           L->d_bnd_part, n_cs, L->bnd_dfac, Qc, lane_q, lane_c, amax);
+                           L->d_bnd_part, n_cs, L->Tp, L->bnd_dfac, Qc, lane_q, lane_c, amax);
         TM_HIP(hipGetLastError());
         return TM_OK;
     };

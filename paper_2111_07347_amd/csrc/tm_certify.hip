@@ -52,6 +52,7 @@ certify_select(const float* __restrict__ Qt, int Tp, int n_valid, const int32_t*
     const double thr_d = static_cast<double>(q_exact[static_cast<size_t>(b) * N + N - 1]) - margin;
     float thr = static_cast<float>(thr_d);
     if (static_cast<double>(thr) > thr_d) thr = nextafterf(thr, -INFINITY);
+    if (thr != thr) thr = -INFINITY;             // no threshold: every template
     const float* row = Qt + static_cast<size_t>(b) * Tp;
     // waves own contiguous quarters, whole groups of V columns (V = 4: one
     // 16-byte load per lane and block; the row length is a multiple of 4)

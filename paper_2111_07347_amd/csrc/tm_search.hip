@@ -45,7 +45,8 @@
 // Rigour in finite precision is that of tm_bound.hip: image and weights
 // rounded up to float16 with exact products, float32 sums widened by 1 / (1 -
 // gamma), the plain path's own rounding covered by the margin c_t A (the
-// sum's first term).
+// sum's first term). A pattern that is too faint for these scales
+// (tm_window.h) is left to the plain scan.
 #include <algorithm>
 #include <array>
 #include <climits>
@@ -57,14 +58,18 @@
 #include "tm_device.h"
 #include "tm_internal.h"
 #include "tm_topn.h"
+#include "tm_window.h"
 
 namespace {
+
+using tmlib::f16_up;
+using tmlib::gamma32;
+using tmlib::h2f;
+using tmlib::kWeightExp;
 
 constexpr int W = 8;                     // windows of shifts per template
 constexpr int kUnit = 4;                 // window records per unit (one 16-byte load)
 constexpr int kExactPad = 8;             // exact records are padded to whole batches of 8
-constexpr int kWeightExp = 10;           // float16 weights carry w * 2^10
-constexpr int kImageExp = 14;            // window maxima scaled below 2^14
 constexpr int kBatch = 64;               // candidates scored between updates of q
 constexpr int kMaxWork = 128;            // largest batch (a histogram bin may hold more)
 constexpr int kSeedPicks = 32;           // columns of Qc that seed the search, about
@@ -130,18 +135,6 @@ struct SearchArgs {
     int* top_s;
     float* top_q;
 };
-
-__device__ __forceinline__ float h2f(uint32_t b) {
-    return static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(b)));
-}
-
-// float16 bits of the smallest float16 >= x (x >= 0; past the range: inf).
-__device__ __forceinline__ uint32_t f16_up(float x) {
-    const _Float16 h = static_cast<_Float16>(x);
-    uint16_t b = __builtin_bit_cast(uint16_t, h);
-    if (static_cast<float>(h) < x) ++b;
-    return b;
-}
 
 struct Ctl {
     int cnt;                             // candidates listed
@@ -510,6 +503,7 @@ search_kernel(const SearchArgs a) {
         return;
     }
     const float invP = pn > 0.0 ? static_cast<float>(1.0 / pn) : 0.0f;
+    const float invUp = tmlib::inverse_up(pn);
     // A = max |P| over the touched rows
     float A = 0.0f;
     if constexpr (KIND != kQc) {
@@ -548,16 +542,19 @@ search_kernel(const SearchArgs a) {
     // no intensity on the touched rows, or 1 / ||P|| = 0: every score is 0 and
     // the ranking goes by template index, so that the first N are the answer
     const bool flat = !(A > 0.0f) || invP == 0.0f;
-    float scale = 1.0f;
+    // no bounds at this scale: left to the plain scan
+    if (!flat && tmlib::no_window_bounds(A, invUp)) {
+        if (tid == 0) a.give[b * a.parts + part] = 1;
+        return;
+    }
+    const tmlib::WindowScale ws = tmlib::window_scale(A);
+    const float scale = ws.image;
     if (!flat) {
         // ---- the window image, row by row: clamped, scaled, rounded-up
         // float16 values of a row and a halo of H columns in rb, maxima of its
         // aligned blocks of o columns in bm; lane l takes the o columns from
         // x0 = o l: the part that all their windows share, then suffix maxima
         // of the head and prefix maxima of the tail
-        int e = 0;
-        (void)frexpf(A, &e);                 // A = m 2^e, m in [0.5, 1)
-        scale = ldexpf(1.0f, kImageExp - e);
         const int o = (n + 63) / 64;
         const int H = a.wlen + o, nb = (n + H) / o;
         const int q = (a.wlen - o) / o, rq = a.wlen - o - q * o;
@@ -644,16 +641,11 @@ search_kernel(const SearchArgs a) {
     }
     __syncthreads();
     const float Ahat = h2f(f16_up(A * scale));
-    // bound = sum out_scale dfac invP_up (1 + 2^-18): the roundings of these
-    // products are more than restored by the last factor
-    float invUp = 0.0f;
-    if (pn > 0.0) {
-        const double ip = 1.0 / pn;
-        invUp = static_cast<float>(ip);
-        if (static_cast<double>(invUp) < ip) invUp = nextafterf(invUp, INFINITY);
-    }
-    const float out_scale = 1.0f / (scale * static_cast<float>(1 << kWeightExp));   // power of 2
-    const float to_q = a.dfac * invUp * (1.0f + 0x1p-18f);
+    // bound = sum to_p invP_up, to_p = out_scale dfac (1 + 2^-18) (out_scale a
+    // power of 2): the first product is at least the plain path's sum, for the
+    // last factor more than restores its rounding, and the second at least its
+    // score, rounding being monotone (also where 1 / ||P|| is subnormal)
+    const float to_p = ws.undo * (a.dfac * (1.0f + 0x1p-18f));
     if (tid == 0) {
         C.cnt = flat && part == 0 ? N : 0;
         C.q = -INFINITY;
@@ -668,7 +660,7 @@ search_kernel(const SearchArgs a) {
     // listed with their windows (seed: with the best window alone, whatever q).
     auto evaluate = [&](int col, bool seed) {
         const int t = col >= 0 ? a.tid[col] : -1;
-        const float u = (window_sum(a, img, col, Ahat, lane) * out_scale) * to_q;
+        const float u = (window_sum(a, img, col, Ahat, lane) * to_p) * invUp;
         float U = u;
 #pragma unroll
         for (int d = W / 2; d >= 1; d >>= 1) U = fmaxf(U, __shfl_xor(U, d, 64));
@@ -842,7 +834,7 @@ search_kernel(const SearchArgs a) {
         if constexpr (KIND == kAll) {
 #pragma unroll 1
             for (int c = wave; c * 64 < n_ub; c += NW) {
-                const float u = (max_window(a, img, first + c, Ahat, lane) * out_scale) * to_q;
+                const float u = (max_window(a, img, first + c, Ahat, lane) * to_p) * invUp;
                 ub[c * 64 + lane] =
                     static_cast<uint16_t>(a.tid[(first + c) * 64 + lane] >= 0 ? f16_up(u) : kDone);
             }
@@ -850,7 +842,7 @@ search_kernel(const SearchArgs a) {
 #pragma unroll 1
             for (int j0 = wave * G; j0 < n_ub; j0 += NW * G) {
                 const int j = j0 + lane / W;
-                float U = (window_sum(a, img, j < n_ub ? column(j) : -1, Ahat, lane) * out_scale) * to_q;
+                float U = (window_sum(a, img, j < n_ub ? column(j) : -1, Ahat, lane) * to_p) * invUp;
 #pragma unroll
                 for (int d = W / 2; d >= 1; d >>= 1) U = fmaxf(U, __shfl_xor(U, d, 64));
                 if (j < n_ub && (lane & (W - 1)) == 0) ub[j] = static_cast<uint16_t>(f16_up(U));
@@ -1106,19 +1098,6 @@ merge_parts(const double* __restrict__ norms, int B, int parts, int N,
     }
 }
 
-double gamma32(double n) {
-    const double u = std::ldexp(1.0, -24);
-    return n * u / (1.0 - n * u);
-}
-
-uint16_t half_up(float x) {
-    const _Float16 h = static_cast<_Float16>(x);
-    uint16_t b;
-    std::memcpy(&b, &h, 2);
-    if (static_cast<float>(h) < x) ++b;
-    return b;
-}
-
 // Shifts per window and columns per window maximum.
 int window_width(int n) { return (n + W - 1) / W; }
 int window_reach(int n) { return (W + 1) * window_width(n) - n; }
@@ -1224,7 +1203,7 @@ int tmlib::search_prepare(tm_library* L, const std::vector<uint32_t>& recs,
             xrec.push_back(static_cast<uint32_t>(rows[row]) << 20 | row << 10 | k);
             xrec.push_back(bits);
             sector[k / w].push_back((row * w + k % w) |
-                                    static_cast<uint32_t>(half_up(std::ldexp(wt, kWeightExp))) << 16);
+                                    static_cast<uint32_t>(f16_up(std::ldexp(wt, kWeightExp))) << 16);
             wsum += wt;
             ++cnt;
         });
