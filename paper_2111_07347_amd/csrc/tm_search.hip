@@ -503,7 +503,6 @@ search_kernel(const SearchArgs a) {
         return;
     }
     const float invP = pn > 0.0 ? static_cast<float>(1.0 / pn) : 0.0f;
-    const float invUp = tmlib::inverse_up(pn);
     // A = max |P| over the touched rows
     float A = 0.0f;
     if constexpr (KIND != kQc) {
@@ -543,7 +542,7 @@ search_kernel(const SearchArgs a) {
     // the ranking goes by template index, so that the first N are the answer
     const bool flat = !(A > 0.0f) || invP == 0.0f;
     // no bounds at this scale: left to the plain scan
-    if (!flat && tmlib::no_window_bounds(A, invUp)) {
+    if (!flat && tmlib::no_window_bounds(A, invP)) {
         if (tid == 0) a.give[b * a.parts + part] = 1;
         return;
     }
@@ -645,6 +644,7 @@ search_kernel(const SearchArgs a) {
     // power of 2): the first product is at least the plain path's sum, for the
     // last factor more than restores its rounding, and the second at least its
     // score, rounding being monotone (also where 1 / ||P|| is subnormal)
+    const float invUp = tmlib::inverse_up(pn);
     const float to_p = ws.undo * (a.dfac * (1.0f + 0x1p-18f));
     if (tid == 0) {
         C.cnt = flat && part == 0 ? N : 0;

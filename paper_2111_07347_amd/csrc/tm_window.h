@@ -5,7 +5,6 @@
 
 #include <hip/hip_runtime.h>
 
-#include <cfloat>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -40,9 +39,10 @@ __host__ __device__ __forceinline__ float inverse_up(double pn) {
 }
 
 // Whether a pattern with intensities has no window bounds: too faint, or
-// 1 / ||P|| past the range (its scores are infinite).
-__host__ __device__ __forceinline__ bool no_window_bounds(float A, float inv_up) {
-    return A > 0.0f && (A < kFaint || inv_up > FLT_MAX);
+// 1 / ||P|| (rounded either way) at the end of the range, past which its
+// scores are infinite.
+__host__ __device__ __forceinline__ bool no_window_bounds(float A, float inv) {
+    return A > 0.0f && (A < kFaint || inv > 0x1p127f);
 }
 
 __host__ __device__ __forceinline__ float h2f(uint32_t bits16) {
@@ -50,7 +50,7 @@ __host__ __device__ __forceinline__ float h2f(uint32_t bits16) {
 }
 
 // float16 bits of the smallest float16 >= x (x >= 0; past the range: inf).
-__host__ __device__ __forceinline__ uint16_t f16_up(float x) {
+__host__ __device__ __forceinline__ uint32_t f16_up(float x) {
     const _Float16 h = static_cast<_Float16>(x);
     uint16_t b = __builtin_bit_cast(uint16_t, h);
     if (static_cast<float>(h) < x) ++b;
