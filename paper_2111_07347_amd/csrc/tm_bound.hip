@@ -156,7 +156,6 @@ size_t scratch_halves(int n, int win) {
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) const uint16_t lds_u16;
 typedef __attribute__((address_space(3))) const u32x2 lds_u32x2;
 
 // LDS byte address of a record's entry: the record's 16-bit entry number
@@ -202,7 +201,8 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
              const int4* __restrict__ slot_end, const int* __restrict__ part, int n_cs, int Tp,
              float dfac, float* __restrict__ Qc,
              float* __restrict__ lane_q, int32_t* __restrict__ lane_c, float* __restrict__ amax) {
-    extern __shared__ uint16_t m16[];        // window image: pairs of halves
+    extern __shared__ u32x2 entries[];       // window image: 4 halves each, read as one
+    uint16_t* m16 = reinterpret_cast<uint16_t*>(entries);
     __shared__ float red[NW];
     const int b = blockIdx.x;
     // gridDim.y workgroups share a pattern's chunks (a power of 2)
@@ -373,7 +373,7 @@ bound_kernel(const float* __restrict__ polar, const double* __restrict__ norms, 
     // operand non-negative; the three roundings are more than restored by
     // the last factor)
     const float out_scale = ws.undo;            // 1 / (scale 2^10), a power of 2
-    const uint32_t base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u16*)m16));
+    const uint32_t base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u32x2*)entries));
     // the wave's chunks [c_begin, c_end) hold about 1 / (NW gridDim.y) of
     // the units
     // each lane also keeps its largest bound and that bound's column (the

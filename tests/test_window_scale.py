@@ -3,6 +3,7 @@ the host): over every binary exponent of float32, a pattern either has bounds
 whose scales are normal powers of 2 that undo each other, with its scaled
 maximum inside float16, or is left to the exhaustive scan."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -61,3 +62,13 @@ def test_scales_over_all_exponents(tmp_path):
     assert r.returncode == 0, r.stderr
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout
+
+
+def test_window_image_is_declared_in_whole_entries():
+    """The kernel reads the image's entries (4 float16) in one 8-byte LDS read:
+    the dynamic LDS array has to be one of 8-byte elements, which is what
+    places it on an 8-byte boundary behind the kernel's static LDS."""
+    src = open(os.path.join(ROOT, "paper_2111_07347_amd", "csrc", "tm_bound.hip")).read()
+    assert re.findall(r"extern __shared__ (\w+) \w+\[\]", src) == ["u32x2"]
+    assert re.search(r"typedef uint32_t u32x2 __attribute__\(\(ext_vector_type\(2\)\)\)", src)
+    assert re.search(r"lds_u32x2\*\)entries", src)
