@@ -53,3 +53,28 @@ def small_library(n_templates=12, seed=0, max_spots=8, g_max=1.0, with_duplicate
         off.append(off[-1] + n)
     return dict(kx=np.array(kx), ky=np.array(ky), intensity=np.array(I),
                 offsets=np.array(off, dtype=np.int64))
+
+
+def exhaustive(tm, lib, polar, norms, N):
+    """Top-N with every template scored at every shift: the allocation-free
+    entry point, which never searches (tm.match_batch may). The reference of
+    tests of the searches and of the rescoring passes."""
+    import ctypes
+
+    import torch
+    B = polar.shape[0]
+    out = tuple(torch.empty((B, N), dtype=dt, device=polar.device)
+                for dt in (torch.int32, torch.int32, torch.float32))
+    o = tm._Opts(compact_rows=tm._layout(lib, polar))
+    tm._check(tm._lib.tm_match_batch_static(
+        lib._h, polar.data_ptr(), norms.data_ptr(), None, B, ctypes.byref(o), N,
+        *(v.data_ptr() for v in out), None, None, torch.cuda.current_stream().cuda_stream),
+        "tm_match_batch_static")
+    return out
+
+
+def same_rows(a, b):
+    """Bit-identical rows (template, angle, score; NaN equal to itself)."""
+    import torch
+    return len(a) == len(b) and all(torch.equal(x.view(torch.int32), y.view(torch.int32))
+                                    for x, y in zip(a, b))

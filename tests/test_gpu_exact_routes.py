@@ -1,0 +1,83 @@
+"""Every route that promises the plain path's top-N against the exhaustive
+scan of the allocation-free entry point, bit for bit, at sizes that reach the
+route: refinement of the bounds of dense libraries, their certified
+rescoring, and the Fourier kernels' certified rescoring (which run when the
+number of templates scored is asked for)."""
+import numpy as np
+import pytest
+
+from conftest import exhaustive, same_rows, small_library
+from test_gpu_search import _patterns
+
+pytestmark = pytest.mark.gpu
+
+R = 34
+PX = (R - 4) / 1.2
+
+
+@pytest.fixture(scope="module")
+def tm():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    import paper_2111_07347_amd as tm
+    return tm
+
+
+def _library(tm, n_theta, T, max_spots, **kw):
+    lib_np = small_library(T, seed=n_theta + T, max_spots=max_spots, g_min=0.08, g_max=1.1)
+    grid = tm.PolarGrid(R=R, n_theta=n_theta, cx=33.0, cy=35.0)
+    return tm.Library(lib_np["kx"], lib_np["ky"], lib_np["intensity"], lib_np["offsets"], PX, grid,
+                      **kw), lib_np, grid
+
+
+# widths at the ends of what is refined (129 to 384 columns), with and without
+# 8 | n_theta; batches of one workgroup per pattern and of several, and the
+# first that is not refined; templates below and above the least number
+@pytest.mark.parametrize("n_theta,T,max_spots,refined", [
+    (129, 4200, 90, True), (180, 4200, 80, True), (361, 4100, 90, True), (384, 4500, 70, True),
+    (385, 4200, 90, False), (360, 1500, 90, False)])
+def test_dense_libraries(tm, n_theta, T, max_spots, refined):
+    import torch
+    lib, lib_np, grid = _library(tm, n_theta, T, max_spots)
+    info = lib.info()
+    # dense, and of as many templates as the route takes
+    assert info["n_spots"] > 24 * info["n_templates_total"]
+    assert (info["n_templates_total"] >= 8192 and 128 < n_theta <= 384) == refined
+    for B in (1, 3, 40, 128, 129):
+        print("[case] dense", n_theta, T, max_spots, "B", B, flush=True)
+        x = torch.from_numpy(_patterns(lib_np, PX, R, B, seed=B)).cuda()
+        for rows in (lib, None):
+            polar, norms, _ = tm.polar_transform(x, grid, lib=rows)
+            if B > 4:
+                norms[4] = float("nan")
+                polar[4, 0, 0] = float("nan")
+            for N in (1, 5, 64):
+                want = exhaustive(tm, lib, polar, norms, N)
+                nr = torch.zeros(B, dtype=torch.int32, device="cuda")
+                for kw in ({}, dict(coarse="bound"), dict(coarse="bound", n_rescored=nr)):
+                    assert same_rows(tm.match_batch(lib, polar, norms, N, **kw), want), (B, N, kw)
+                assert int(nr.min()) >= 0
+    lib.free()
+
+
+@pytest.mark.parametrize("n_theta,T,max_spots", [(90, 40, 25), (180, 300, 12), (360, 600, 8),
+                                                 (720, 40, 25)])
+def test_fourier_kernels_certified(tm, n_theta, T, max_spots):
+    import torch
+    lib, lib_np, grid = _library(tm, n_theta, T, max_spots, fft=True)
+    for B in (1, 5, 65, 130):
+        print("[case] fourier", n_theta, T, max_spots, "B", B, flush=True)
+        x = torch.from_numpy(_patterns(lib_np, PX, R, B, seed=B)).cuda()
+        for rows in (lib, None):
+            polar, norms, _ = tm.polar_transform(x, grid, lib=rows)
+            if B > 4:
+                norms[4] = float("nan")
+                polar[4, 0, 0] = float("nan")
+            for N in (1, 5):
+                want = exhaustive(tm, lib, polar, norms, N)
+                nr = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+                got = tm.match_batch(lib, polar, norms, N, coarse="fft", n_rescored=nr)
+                assert same_rows(got, want), (B, N)
+                live = torch.isfinite(norms)
+                assert int(nr[live].min()) >= N and int(nr.max()) <= lib.n_total
+    lib.free()

@@ -10,6 +10,7 @@ import pytest
 
 import oracle
 import synth
+from conftest import exhaustive, same_rows
 from parity import PatternRef, check_topn, oracle_best_pool, scores_close
 
 pytestmark = pytest.mark.gpu
@@ -120,6 +121,49 @@ def test_full_scan_sampled_against_oracle(cid, n_sample):
         t1, s1, q1 = (o.cpu().numpy()[0] for o in tm.match_batch(lib, p1, n1, cfg.N))
         assert np.array_equal(t1, tt[b]) and np.array_equal(s1, ts[b]) and np.array_equal(q1, tq[b])
 
+
+def test_fcc_scan_every_route_equals_exhaustive():
+    """FCC scan: the searches (plain path, bound route), the certified passes
+    and the Fourier kernels' certified rescoring (both asked for by the number
+    of templates they score) give the exhaustive scan's rows on every
+    pattern, bit for bit."""
+    import torch
+    sc = _scan(2)
+    tm, cfg, lib_np, grid, px = (sc[k] for k in ("tm", "cfg", "lib_np", "grid", "px"))
+    lib, polar, norms = sc["lib"], sc["polar"], sc["norms"]
+    want = exhaustive(tm, lib, polar, norms, cfg.N)
+    assert same_rows([torch.from_numpy(v).cuda() for v in sc["top"]], want)
+    flib = tm.Library(lib_np["kx"], lib_np["ky"], lib_np["intensity"], lib_np["offsets"], px, grid,
+                      fft=True)
+    for name, use, kw in (("bound", lib, dict(coarse="bound")), ("fourier or plain", flib, dict(coarse="fft")),
+                          ("certified", lib, dict(coarse="bound", n_rescored=None)),
+                          ("fourier certified", flib, dict(coarse="fft", n_rescored=None))):
+        if "n_rescored" in kw:
+            kw["n_rescored"] = torch.zeros(cfg.B, dtype=torch.int32, device="cuda")
+        _say("FCC scan against the exhaustive one:", name)
+        assert same_rows(tm.match_batch(use, polar, norms, cfg.N, **kw), want), name
+        if "n_rescored" in kw:
+            assert int(kw["n_rescored"].min()) >= cfg.N
+    flib.free()
+
+
+def test_c3_scan_every_route_equals_exhaustive():
+    """20 000-template scan: the plain path, the bound route and the certified
+    passes give the exhaustive scan's rows on every pattern, bit for bit; so
+    do 1 and 128 of them (refined), 129 and 256 (certified)."""
+    import torch
+    sc = _scan(3)
+    tm, cfg, lib, polar, norms = (sc[k] for k in ("tm", "cfg", "lib", "polar", "norms"))
+    _say("C3 scan, exhaustive")
+    want = exhaustive(tm, lib, polar, norms, cfg.N)
+    assert same_rows([torch.from_numpy(v).cuda() for v in sc["top"]], want)
+    for B in (1, 128, 129, 256, cfg.B):
+        _say("C3 scan against the exhaustive one:", B)
+        p, n, w = polar[:B], norms[:B], [v[:B] for v in want]
+        nr = torch.zeros(B, dtype=torch.int32, device="cuda")
+        for kw in ({}, dict(coarse="bound"), dict(coarse="bound", n_rescored=nr)):
+            assert same_rows(tm.match_batch(lib, p, n, cfg.N, **kw), w), (B, kw)
+        assert int(nr.min()) >= cfg.N
 
 
 def test_c3_scan_sampled_against_oracle_pool():
