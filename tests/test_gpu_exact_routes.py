@@ -81,3 +81,27 @@ def test_fourier_kernels_certified(tm, n_theta, T, max_spots):
                 live = torch.isfinite(norms)
                 assert int(nr[live].min()) >= N and int(nr.max()) <= lib.n_total
     lib.free()
+
+
+@pytest.mark.parametrize("share", [1, 3])
+def test_patterns_without_structure(tm, share):
+    """Patterns of which most templates' bounds reach the best scores are given
+    up and scanned in full: each in several tasks, or, from 1025 of them on,
+    in one."""
+    import torch
+    lib, lib_np, grid = _library(tm, 360, 1300, 8)
+    for B in (1, 40, 1024, 1025, 2049):
+        print("[case] noise", share, "B", B, flush=True)
+        x = np.resize(_patterns(lib_np, PX, R, min(B, 128), seed=B), (B, 70, 66)).astype(np.float32)
+        x[::share] = np.random.default_rng(B).standard_normal(x[::share].shape)
+        polar, norms, prof = tm.polar_transform(torch.from_numpy(x).cuda(), grid)
+        for N in (1, 5, 64):
+            want = exhaustive(tm, lib, polar, norms, N)
+            for kw in ({}, dict(coarse="bound"),
+                       dict(coarse="bound", n_rescored=torch.zeros(B, dtype=torch.int32, device="cuda"))):
+                assert same_rows(tm.match_batch(lib, polar, norms, N, **kw), want), (B, N, kw)
+        kept = tm.prefilter(lib, prof, 650, "fp32")
+        cand = torch.cat([kept, kept + 1300], 1).contiguous()
+        got = tm.match_batch(lib, polar, norms, 5, profiles=prof, prefilter_keep=0.5)
+        assert same_rows(got, tm.match_candidates(lib, polar, norms, cand, 5)), B
+    lib.free()
