@@ -50,22 +50,55 @@ constexpr int kWavesShared = 8;
 constexpr int kWavesWhole = 16;
 constexpr size_t kWholeCuLds = 80 * 1024;
 
-// Small batches: workgroups that share the patterns' groups, at least
+// Small batches: workgroups that share a pattern's groups, at least
 // kPartGroups groups per wave of each (twice that where a workgroup stages a
-// CU's whole LDS). One workgroup per pattern leaves CUs idle or with two waves
-// per SIMD, which wait for record loads. 200 patterns, 16 000 templates with
-// all scores written: 1570 us in 1 part, 820 in 3, 655 in 10, 663 in 16; 64
-// patterns, 600 templates: 84 us in 1 part, 68 in 6 (with the polar transform).
-// What the split and its merge cost (10 us) is saved from kSplitWork vector
-// instructions of a scan on: 198 FCC templates on 157 columns, 2e4 of them, take
-// 56 us whole and 65 split, 300 on 360 columns, 5e4, 84 and 68. Where the rows
-// fill a CU's LDS the patterns alone fill the chip sooner: 483 patterns,
-// 766 orthorhombic templates, 1.84 ms whole and 2.13 in four parts.
-constexpr int32_t kSplitGrid = 2048;
-constexpr int32_t kSplitWhole = 512;
+// CU's whole LDS), at most kMaxParts, from kSplitWork vector instructions of a
+// scan on (below, the split and its merge cost what they save).
 constexpr int64_t kSplitWork = 32768;
+constexpr int64_t kLongScan = 500000;
 constexpr int32_t kPartGroups = 2;
 constexpr int32_t kMaxParts = 16;
+constexpr int32_t kCus = 256;
+
+// Workgroups per pattern of a scan of `work` vector instructions; every part
+// stages the rows again, and a merge follows. One workgroup per pattern leaves
+// CUs idle, or with two waves per SIMD that wait for record loads; it is best
+// where the patterns alone fill the chip (the `room` of workgroups that its
+// LDS and wave slots hold). Measured (us: one part, split), all scores written
+// where the work is weighted:
+//   whole LDS: up to a workgroup per CU no more than that (688 thousand
+//   instructions, 64 patterns 413, 178; 200: 414, 441 in 2), just above it the
+//   parts even out the last round (320: 816, 614 in 4; 512: 833, 873 in 2);
+//   else three workgroups per CU for few patterns (55 thousand: 64 patterns 82,
+//   54, 128: 81, 65), two to eight per CU where the scan is long (414 thousand
+//   with scores, 200 patterns: 694, 347 in 10; 163 thousand, 256: 184, 156 in
+//   3), none for short ones (55 thousand, 256: 82, 99 in 8; 512: 107, 132 in
+//   4), but three parts just above a workgroup per CU (320: 104, 99).
+int32_t split_parts(int32_t B, int64_t work, int32_t n_groups, int nw, size_t lds_bytes, bool scores) {
+    if (work < kSplitWork) return 1;
+    const bool whole = nw == kWavesWhole;
+    const int64_t w = scores ? work + work / 2 : work;
+    const int64_t room = kCus * std::min<int64_t>(4, static_cast<int64_t>(160 * 1024 / lds_bytes));
+    int64_t grid;
+    if (whole && B <= kCus) {
+        // one round of the chip, or two where that leaves fewer CUs idle
+        const int one = kCus / B, two = 2 * kCus / B;
+        grid = w >= kLongScan && 93 * two > 200 * one ? 2 * kCus : kCus;
+    } else if (whole)
+        grid = B <= kCus + kCus / 2 ? 4 * B : B;
+    else if (B >= room)
+        grid = B;
+    else if (B <= kCus / 2)
+        grid = 3 * kCus;
+    else if (w >= (B <= kCus ? 400000 : 200000))
+        grid = 8 * kCus;
+    else if (B <= kCus)
+        grid = w >= 100000 ? 4 * kCus : B;
+    else
+        grid = B <= kCus * 7 / 4 ? 3 * B : B;
+    const int64_t most = std::min(n_groups / (kPartGroups * nw * (1 + whole)), kMaxParts);
+    return static_cast<int32_t>(std::max<int64_t>(1, std::min(grid / B, most)));
+}
 
 // Records x patterns of a plain scan below which the Fourier route's dozen
 // launches do not pay.
@@ -493,10 +526,8 @@ int tmlib::launch_match(const tm_library* lib, const float* polar, const double*
     const int32_t n_groups = cand ? n_items : lib->n_groups;
     const tmlib::SplitWork work = split ? *split : tmlib::SplitWork{};
     int32_t parts = 1;
-    if (may_allocate && !cand && !split && !pat_mask && lib->n_records * (1 + G * K) >= kSplitWork) {
-        const int whole = nw == kWavesWhole;
-        parts = std::max(1, std::min({(whole ? kSplitWhole : kSplitGrid) / B, n_groups / (kPartGroups * nw * (1 + whole)), kMaxParts}));
-    }
+    if (may_allocate && !cand && !split && !pat_mask)
+        parts = split_parts(B, lib->n_records * (1 + G * K), n_groups, nw, lds_bytes, best_score != nullptr);
     tmlib::Scratch mem;
     int32_t *out_t = top_template, *out_s = top_angle;
     float* out_q = top_score;

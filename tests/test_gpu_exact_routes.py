@@ -105,3 +105,35 @@ def test_patterns_without_structure(tm, share):
         got = tm.match_batch(lib, polar, norms, 5, profiles=prof, prefilter_keep=0.5)
         assert same_rows(got, tm.match_candidates(lib, polar, norms, cand, 5)), B
     lib.free()
+
+
+# batches around a workgroup per compute unit (256), half and one and a half
+# of that, and what a compute unit's LDS holds; libraries whose rows leave room
+# for several workgroups or fill it, short scans and long ones
+@pytest.mark.parametrize("n_theta,rows,T,max_spots", [(360, 34, 200, 12), (180, 34, 1500, 12),
+                                                      (360, 48, 70, 60), (361, 60, 400, 90)])
+def test_scans_split_over_workgroups(tm, n_theta, rows, T, max_spots):
+    import torch
+    lib_np = small_library(T, seed=n_theta + T, max_spots=max_spots, g_min=0.08, g_max=1.1)
+    px = (rows - 4) / 1.2
+    grid = tm.PolarGrid(R=rows, n_theta=n_theta, cx=33.0, cy=35.0)
+    lib = tm.Library(lib_np["kx"], lib_np["ky"], lib_np["intensity"], lib_np["offsets"], px, grid)
+    x = torch.from_numpy(_patterns(lib_np, px, rows, 96, seed=7)).cuda()
+    every, nall, _ = tm.polar_transform(x, grid, lib=lib)
+    nall[4] = float("nan")
+    every[4, 0, 0] = float("nan")
+    for B in (1, 2, 44, 100, 128, 129, 256, 257, 384, 385, 448, 449, 513, 1025):
+        print("[case] split", n_theta, rows, T, "B", B, flush=True)
+        at = torch.arange(B, device="cuda") % 96
+        polar, norms = every[at].contiguous(), nall[at].contiguous()
+        N = min(7, 2 * T)
+        want = exhaustive(tm, lib, polar, norms, N)
+        got = tm.match_batch(lib, polar, norms, N, with_best=True)
+        assert same_rows(got[:3], want), B
+        assert same_rows(tm.match_batch(lib, polar, norms, N), want), B
+        live = torch.isfinite(norms)
+        assert torch.equal(got[3][live].amax(1), want[2][live][:, 0]), B
+        assert torch.equal(got[3][live].gather(1, want[0][live].long()), want[2][live]), B
+        assert torch.equal(got[4][live].gather(1, want[0][live].long()).int(), want[1][live]), B
+        assert bool(got[3][~live].isnan().all()) and bool((got[4][~live] == -1).all())
+    lib.free()
