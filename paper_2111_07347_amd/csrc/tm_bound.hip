@@ -105,6 +105,7 @@ namespace {
 using tmlib::f16_up;
 using tmlib::gamma32;
 using tmlib::h2f;
+using tmlib::kSearchWindows;
 using tmlib::kWeightExp;
 
 constexpr int kShifts = 4;                 // coarse shifts per template
@@ -116,12 +117,10 @@ constexpr size_t kLdsBudget = 128 * 1024;  // window image (16-bit offsets)
 constexpr int kFirst = 48;                 // best bounds scored exactly first
 constexpr int kBuildWaves = 8;             // waves that build the window image's rows
 constexpr int kParts = 1024;               // chunk ranges (waves x workgroups of a pattern)
-constexpr int64_t kSearchRecords = 8192;   // records of a plain scan from which the search pays
-constexpr int64_t kSearchWork = 3000000;   //   for a sparse library, whatever the batch (records x
-constexpr int64_t kBoundRecords = 131072;  //   patterns otherwise), and for the others (766 ortho-
-                                           //   rhombic templates, 483 patterns: 1.8 ms scanned, 2.1
-                                           //   searched; 999, 52 patterns, 720 columns: 1.0 and 2.2;
-                                           //   3000, 512 patterns: 0.9 searched)
+constexpr int64_t kBoundRecords = 131072;  // records from which a search of a dense library pays
+                                           //   (766 orthorhombic templates, 483 patterns: 1.8 ms
+                                           //   scanned, 2.1 searched; 999, 52 patterns, 720 columns:
+                                           //   1.0 and 2.2; 3000, 512 patterns: 0.9 searched)
 constexpr int32_t kSearchChunk = 65536;    // patterns of a plain path's search at a time, and
 constexpr size_t kSearchScratch = size_t(4) << 30;   // the bytes of their bounds
 constexpr int kFillGrid = 512;             // workgroups that fill the chip (two per CU)
@@ -137,6 +136,10 @@ constexpr int kRefineColumns[2] = {128, 384};
 constexpr int kFewColumns = 192;           // few columns, many pixels per template, many
 constexpr int64_t kManySpots = 10;         //   patterns (see searches_all)
 constexpr int32_t kManyPatterns = 512;
+constexpr int kSomeColumns = 300;          // the same for few templates and
+constexpr int32_t kMostPatterns = 2048;    //   very many patterns
+constexpr int32_t kFewTemplates = 4000;
+constexpr int32_t kLoosePatterns = 128;    // patterns from which loose windows do not pay
 constexpr int kMaxSplit = 32;              // workgroups per pattern of a small batch
 constexpr int kMaxCols = 12;               // window columns per lane (n_theta <= 768)
 
@@ -864,11 +867,21 @@ int bound_split(const tm_library* L, int32_t B) {
 // cannot fill the chip with its passes (21 of them, 3897 templates: 238
 // against 455 us); nor on more than six columns per lane (720 columns, 1000 to
 // 8000 templates, 8 and 32 patterns: 186 to 540 us against 137 to 506; FCC:
-// 118 to 331 against 257 to 467).
+// 118 to 331 against 257 to 467). Nor for many patterns and few such
+// templates below 300 columns (600 and 2400 templates, 4096 patterns, 220 to
+// 256 columns: 646 to 831 us searched, 519 to 648 certified), nor where the
+// columns are so few over a multiple of the windows that their maxima reach
+// far past them (90 columns, windows of 12, maxima of 18; FCC, 600 to 24 000
+// templates, 512 and 4096 patterns: 201 to 1174 and 648 to 5047 us against
+// 159 to 1110 and 467 to 4227; 72 and 110 columns: 0.6 to 1.0 of the certified
+// passes).
 bool searches_all(const tm_library* L, int32_t B) {
+    const int n = L->n_theta, w = (n + kSearchWindows - 1) / kSearchWindows;
+    const bool loose = 4 * (kSearchWindows * w - n) > w && B >= kLoosePatterns;
+    const bool few_columns = n <= kFewColumns ? B >= kManyPatterns
+                                              : n <= kSomeColumns && B >= kMostPatterns && L->Tp <= kFewTemplates;
     const bool many = L->n_spots >= kManySpots * L->Tp;
-    const bool few_columns = L->n_theta <= kFewColumns && B >= kManyPatterns;
-    return L->sr_all && !(many && (few_columns || L->n_theta > kRefineColumns[1]));
+    return L->sr_all && !loose && !(many && (few_columns || n > kRefineColumns[1]));
 }
 
 }  // namespace
@@ -965,12 +978,28 @@ int tmlib::bound_match(const tm_library* lib, const float* polar, const double* 
     return mem.release(s, r);
 }
 
-// The plain path's top-N by the window-bound search, where that pays and its
-// scratch can be had: patterns in chunks of bounded scratch.
+// Whether the plain path finds its top-N by the window-bound search. A sparse
+// library's search costs a pattern a fixed part (window image, bounds of all
+// templates, seeds) in a chain of short phases, which few patterns do not
+// hide, while their scan spreads over the chip: the search is faster from some
+// b b w on, b the patterns and w the vector instructions of a scan. Few columns
+// make narrow windows of loose bounds, few templates a scan that is cheaper
+// than the fixed part, many pixels per template a dearer one. Measured (us:
+// scanned, searched; 256 x 256 patterns, 360 columns but where stated): 2000 FCC
+// templates (w 246 thousand), 64 patterns 104, 188; 192: 201, 197; 2048: 1128,
+// 399; 8000 HCP (1.6 million), 32: 222, 382; 128: 582, 411; 2048: 6701, 1311; 300
+// FCC (55 thousand), 1024: 179, 182; 2048: 310, 243; 100 FCC, 4096: 291, 335; 300
+// HCP on 240 columns (62 thousand), 1024: 188, 287; 4096: 596, 520; 1200 FCC on
+// 180 (76 thousand), 512: 182, 203; 2048: 500, 349; 2000 FCC on 90 (77
+// thousand), 4096: 1150, 1388; 6000 (210 thousand), 1024: 893, 1037; 4096: 2965,
+// 2318; 3000 HCP (216 thousand), 512: 408, 609; 1024: 682, 599.
 bool tmlib::search_pays(const tm_library* lib, int32_t B) {
-    if (lib->sr_all)
-        return lib->n_records >= kSearchRecords || static_cast<int64_t>(B) * lib->n_records >= kSearchWork;
-    return lib->bound && lib->n_records >= kBoundRecords && lib->n_theta > kRefineColumns[0];
+    if (!lib->sr_all) return lib->bound && lib->n_records >= kBoundRecords && lib->n_theta > kRefineColumns[0];
+    const double b = B, w = static_cast<double>(lib->n_records) * (1 + lib->group * slots_for(lib->n_theta));
+    if (lib->n_theta <= 128) return w >= 9e4 && b * w >= 2.2e8 && b * b * w >= 5e10;
+    const bool large = w >= 1e5 && lib->n_spots < kManySpots * lib->Tp;
+    if (lib->n_theta <= kFewColumns) return b * b * w >= 2.4e10 && (large || (w >= 6e4 && b * w >= 8e7));
+    return b * b * w >= 1e10 && (large || (lib->n_records >= 2500 && b * w >= 8e7));
 }
 
 int tmlib::search_top(const tm_library* lib, const float* polar, const double* norms, int32_t B,

@@ -100,8 +100,11 @@ int32_t split_parts(int32_t B, int64_t work, int32_t n_groups, int nw, size_t ld
     return static_cast<int32_t>(std::max<int64_t>(1, std::min(grid / B, most)));
 }
 
-// Records x patterns of a plain scan below which the Fourier route's dozen
-// launches do not pay.
+// Records, or records x patterns, of a sparse library from which the plain path
+// is faster than the Fourier route (searched or scanned), and records x patterns
+// below which it is for any library: the route takes a dozen launches.
+constexpr int64_t kSparseRecords = 8192;
+constexpr int64_t kSparseWork = 3000000;
 constexpr int64_t kScanWork = 1500000;
 
 // One union pixel of a group: LDS float offset within the band, then one
@@ -666,7 +669,9 @@ int tmlib::match_batch_impl(const tm_library* lib, const float* polar, const dou
     // (300 FCC templates, 64 patterns: 212 -> 59 us; 100 orthorhombic ones,
     // 300 patterns, 2e6 records: 218 -> 224, beyond the rule).
     if (coarse == TM_COARSE_FFT && policy == TM_RESCORE_CERTIFIED && !n_rescored && may_allocate &&
-        (tmlib::search_pays(lib, B) || static_cast<int64_t>(B) * lib->n_records < kScanWork))
+        ((lib->sr_all ? lib->n_records >= kSparseRecords || static_cast<int64_t>(B) * lib->n_records >= kSparseWork
+                      : tmlib::search_pays(lib, B)) ||
+         static_cast<int64_t>(B) * lib->n_records < kScanWork))
         coarse = TM_COARSE_NONE;
     if (coarse == TM_COARSE_FFT)
         return tmlib::fft_match(lib, polar, norms, B, N, policy, rescore_keep, n_rescored,

@@ -67,7 +67,7 @@ using tmlib::gamma32;
 using tmlib::h2f;
 using tmlib::kWeightExp;
 
-constexpr int W = 8;                     // windows of shifts per template
+constexpr int W = tmlib::kSearchWindows; // windows of shifts per template
 constexpr int kUnit = 4;                 // window records per unit (one 16-byte load)
 constexpr int kExactPad = 8;             // exact records are padded to whole batches of 8
 constexpr int kBatch = 64;               // candidates scored between updates of q

@@ -13,6 +13,7 @@ namespace tmlib {
 
 constexpr int kWeightExp = 10;           // float16 weights carry w * 2^10
 constexpr int kImageExp = 14;            // window maxima are scaled below 2^14
+constexpr int kSearchWindows = 8;        // windows of shifts per template of the search
 
 // Least A = max |P| with window bounds. From here on the scales of
 // window_scale and the sums they undo are normal float32 numbers, and what

@@ -137,3 +137,26 @@ def test_scans_split_over_workgroups(tm, n_theta, rows, T, max_spots):
         assert torch.equal(got[4][live].gather(1, want[0][live].long()).int(), want[1][live]), B
         assert bool(got[3][~live].isnan().all()) and bool((got[4][~live] == -1).all())
     lib.free()
+
+
+# on either side of the rule that sends the plain path of a sparse library to
+# its search, and of those that leave the search for the certified passes (few
+# columns over a multiple of the windows, many pixels per template)
+@pytest.mark.parametrize("n_theta,T,max_spots,Bs", [
+    (90, 2200, 8, (64, 127, 128, 700, 1500)), (72, 2200, 8, (128, 1500)), (180, 1500, 8, (300, 700, 1400)),
+    (220, 900, 34, (500, 2047, 2048)), (360, 700, 8, (60, 300, 900, 1700)), (720, 600, 34, (100, 300, 900))])
+def test_sparse_libraries_by_scan_search_or_certified(tm, n_theta, T, max_spots, Bs):
+    import torch
+    lib, lib_np, grid = _library(tm, n_theta, T, max_spots)
+    assert lib.info()["n_spots"] <= 24 * lib.n_total
+    x = torch.from_numpy(_patterns(lib_np, PX, R, 96, seed=3)).cuda()
+    every, nall, _ = tm.polar_transform(x, grid, lib=lib)
+    for B in Bs:
+        print("[case] sparse", n_theta, T, max_spots, "B", B, flush=True)
+        at = torch.arange(B, device="cuda") % 96
+        polar, norms = every[at].contiguous(), nall[at].contiguous()
+        for N in (1, 6):
+            want = exhaustive(tm, lib, polar, norms, N)
+            for kw in ({}, dict(coarse="bound")):
+                assert same_rows(tm.match_batch(lib, polar, norms, N, **kw), want), (B, N, kw)
+    lib.free()
