@@ -102,10 +102,21 @@ int32_t split_parts(int32_t B, int64_t work, int32_t n_groups, int nw, size_t ld
 
 // Records, or records x patterns, of a sparse library from which the plain path
 // is faster than the Fourier route (searched or scanned), and records x patterns
-// below which it is for any library: the route takes a dozen launches.
+// below which it is for any library: the route takes a dozen launches. Of a dense
+// library it depends on the patterns: without a clear best template they are
+// scanned in full, which takes twice the route's time. That becomes common
+// where a template has more than a pixel per touched row, so that a quarter
+// turn of nearly every row holds a spot (orthorhombic templates of 76 pixels,
+// 256 patterns, us by plain path and route: 53 rows, 28 000 templates 11404,
+// 4596, 8000: 3388, 1470; 64 rows: 6325, 4599 and 1267, 1514; 76: 1685, 5212 and
+// 897, 1682; 95: 528, 5365 and 350, 1775): up to kRowPixels per row, or up to so
+// many patterns x templates x columns that the route's launches count (37 778
+// templates on 720 columns, one pattern: 4.9 ms, 6.1).
 constexpr int64_t kSparseRecords = 8192;
 constexpr int64_t kSparseWork = 3000000;
 constexpr int64_t kScanWork = 1500000;
+constexpr double kRowPixels = 1.08;
+constexpr int64_t kDenseWork = 150000000;
 
 // One union pixel of a group: LDS float offset within the band, then one
 // weight per group member.
@@ -664,13 +675,15 @@ int tmlib::match_batch_impl(const tm_library* lib, const float* polar, const dou
     // path, whatever the spectra say; unless the caller asks for the number
     // of certified templates, the plain path gives them sooner where its
     // search with bounds pays (8000 HCP templates: 512 patterns 4979 ->
-    // 553 us, 8 of them at half the size 534 -> 220; 3000 orthorhombic ones:
+    // 553 us, 8 of them at half the size 534 -> 158; 3000 orthorhombic ones:
     // 512 patterns 2741 -> 898, 4 of them 489 -> 231) or the scan is small
     // (300 FCC templates, 64 patterns: 212 -> 59 us; 100 orthorhombic ones,
     // 300 patterns, 2e6 records: 218 -> 224, beyond the rule).
     if (coarse == TM_COARSE_FFT && policy == TM_RESCORE_CERTIFIED && !n_rescored && may_allocate &&
         ((lib->sr_all ? lib->n_records >= kSparseRecords || static_cast<int64_t>(B) * lib->n_records >= kSparseWork
-                      : tmlib::search_pays(lib, B)) ||
+                      : tmlib::search_pays(lib, B) &&
+                            (static_cast<double>(lib->n_spots) <= kRowPixels * lib->n_rows * lib->Tp ||
+                             static_cast<int64_t>(B) * lib->Tp <= kDenseWork / lib->n_theta)) ||
          static_cast<int64_t>(B) * lib->n_records < kScanWork))
         coarse = TM_COARSE_NONE;
     if (coarse == TM_COARSE_FFT)

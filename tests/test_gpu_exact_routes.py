@@ -160,3 +160,18 @@ def test_sparse_libraries_by_scan_search_or_certified(tm, n_theta, T, max_spots,
             for kw in ({}, dict(coarse="bound")):
                 assert same_rows(tm.match_batch(lib, polar, norms, N, **kw), want), (B, N, kw)
     lib.free()
+
+
+def test_dense_fourier_calls_by_either_route(tm):
+    """Certified Fourier calls without counts: a dense library's take the plain
+    path up to a number of patterns (99 of these), the kernels beyond."""
+    import torch
+    lib, lib_np, grid = _library(tm, 180, 4200, 80, fft=True)
+    assert lib.info()["n_spots"] > 24 * lib.n_total
+    x = torch.from_numpy(_patterns(lib_np, PX, R, 110, seed=5)).cuda()
+    polar, norms, _ = tm.polar_transform(x, grid, lib=lib)
+    for B in (1, 99, 100, 110):
+        print("[case] dense fourier, B", B, flush=True)
+        p, n = polar[:B], norms[:B]
+        assert same_rows(tm.match_batch(lib, p, n, 5, coarse="fft"), exhaustive(tm, lib, p, n, 5)), B
+    lib.free()
