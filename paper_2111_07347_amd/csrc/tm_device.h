@@ -12,14 +12,15 @@ __device__ __forceinline__ int lane_id() { return __lane_id(); }
 // Uniform (scalar) copy of a wave-uniform value.
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// The wave's maximum (no NaN): along the rows of 16 lanes, then across them
-// (data-parallel moves of the vector unit; the LDS crossbar, which shuffles
-// go through, takes ten times as long per step), read from the last lane.
-__device__ __forceinline__ float wave_max(float v) {
+// v combined over the wave's lanes by f, in all of them: along the rows of 16
+// lanes, then across them (data-parallel moves of the vector unit; the LDS
+// crossbar, which shuffles go through, takes ten times as long per step), read
+// from the last lane. A lane without a partner combines its value with itself,
+// so f(x, x) has to be x (a maximum or minimum).
+template <typename F>
+__device__ __forceinline__ int wave_fold(int v, F f) {
     auto step = [&](auto ctrl, auto rows) {
-        const int o = __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), ctrl.value,
-                                                  rows.value, 0xf, false);
-        v = fmaxf(v, __int_as_float(o));
+        v = f(v, __builtin_amdgcn_update_dpp(v, v, ctrl.value, rows.value, 0xf, false));
     };
     using std::integral_constant;
     step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});    // row_shr:1
@@ -28,7 +29,14 @@ __device__ __forceinline__ float wave_max(float v) {
     step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});    // row_shr:8
     step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});    // row_bcast:15
     step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});    // row_bcast:31
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
+// The wave's maximum (no NaN).
+__device__ __forceinline__ float wave_max(float v) {
+    return __int_as_float(wave_fold(__float_as_int(v), [](int x, int y) {
+        return __float_as_int(fmaxf(__int_as_float(x), __int_as_float(y)));
+    }));
 }
 
 __device__ __forceinline__ double wave_sum(double v) {

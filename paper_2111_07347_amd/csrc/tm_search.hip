@@ -156,25 +156,6 @@ struct Lists {
     Ctl ctl;
 };
 
-// x combined over the wave's lanes, in all lanes: DPP moves that bring each
-// row's result to its last lane, then lane 63.
-template <typename F>
-__device__ __forceinline__ int wave_fold(int v, F f) {
-    v = f(v, __builtin_amdgcn_update_dpp(v, v, 0x111, 0xf, 0xf, false));    // row_shr 1, 2, 4, 8
-    v = f(v, __builtin_amdgcn_update_dpp(v, v, 0x112, 0xf, 0xf, false));
-    v = f(v, __builtin_amdgcn_update_dpp(v, v, 0x114, 0xf, 0xf, false));
-    v = f(v, __builtin_amdgcn_update_dpp(v, v, 0x118, 0xf, 0xf, false));
-    v = f(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xf, 0xf, false));    // row_bcast 15, 31
-    v = f(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xf, 0xf, false));
-    return __builtin_amdgcn_readlane(v, 63);
-}
-
-__device__ __forceinline__ float wave_top(float v) {
-    return __int_as_float(wave_fold(__float_as_int(v), [](int x, int y) {
-        return __float_as_int(fmaxf(__int_as_float(x), __int_as_float(y)));
-    }));
-}
-
 // Suffix sums over a histogram of 64 bins (one wave): the highest bin from
 // which on there are at least `want` entries, 0 if there is none.
 __device__ __forceinline__ int cut_bin(const int* hist, int want, int lane) {
@@ -255,8 +236,8 @@ __device__ __forceinline__ float exact_lds(const SearchArgs& a, const float* __r
             bs = sh;
         }
     }
-    const float wm = wave_top(bm);
-    best_s = wave_fold(bm == wm ? bs : INT_MAX, [](int x, int y) { return min(x, y); });
+    const float wm = tmlib::wave_max(bm);
+    best_s = tmlib::wave_fold(bm == wm ? bs : INT_MAX, [](int x, int y) { return min(x, y); });
     return wm;
 }
 
@@ -314,7 +295,7 @@ __device__ __forceinline__ void exact_windows(const SearchArgs& a, const float* 
 #pragma unroll
         for (int k = 0; k < V; ++k) {
             const float v = d < a.w && sh0[k] + d < a.n ? acc[k] : -INFINITY;
-            const float wm = wave_top(v);
+            const float wm = tmlib::wave_max(v);
             const int s = sh0[k] + d0 + __ffsll(static_cast<long long>(tmlib::ballot(v == wm))) - 1;
             if (wm > best || (wm == best && s < bs)) {
                 best = wm;
@@ -530,7 +511,7 @@ search_kernel(const SearchArgs a) {
                 }
             }
         }
-        A = wave_top(A);
+        A = tmlib::wave_max(A);
         if (lane == 0) red[wave] = A;
         __syncthreads();
 #pragma unroll
@@ -941,7 +922,7 @@ search_kernel(const SearchArgs a) {
             const size_t lo = static_cast<size_t>(b) * a.n_list;
             float m = 0.0f;
             for (int i = tid; i < a.n_list; i += NT) m = fmaxf(m, a.lq[lo + i]);
-            m = wave_top(m);
+            m = tmlib::wave_max(m);
             if (lane == 0) red[wave] = m;
             if (tid < 64) C.hist[tid] = 0;
             if (tid == 0) {
