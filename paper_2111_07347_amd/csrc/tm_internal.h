@@ -38,7 +38,8 @@ public:
     template <typename T>
     void add(T*& p, size_t n) {
         p = nullptr;
-        slots_.push_back({&p, bytes_});
+        if (n_ < kArrays) slots_[n_] = {&p, bytes_};
+        ++n_;
         bytes_ += (std::max<size_t>(n, 1) * sizeof(T) + 255) / 256 * 256;
     }
     // TM_ENOMEM with a message when there is no such memory.
@@ -49,7 +50,9 @@ public:
 
 private:
     struct Slot { void* p; size_t at; };
-    std::vector<Slot> slots_;
+    static constexpr int kArrays = 24;           // (in place: nothing here throws)
+    Slot slots_[kArrays];
+    int n_ = 0;
     size_t bytes_ = 0;
     char* base_ = nullptr;
 };

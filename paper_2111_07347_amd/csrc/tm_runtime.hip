@@ -26,15 +26,19 @@ int hip_fail(hipError_t e, const char* what) {
 }
 
 int Scratch::allocate(hipStream_t s) {
+    if (n_ > kArrays) {
+        set_error("scratch of %d arrays, room for %d", n_, kArrays);
+        return TM_EUNSUPPORTED;
+    }
     hipError_t e = hipMallocAsync(reinterpret_cast<void**>(&base_), std::max<size_t>(bytes_, 256), s);
     if (e != hipSuccess) {
         base_ = nullptr;
         set_error("hipMallocAsync(%zu bytes) failed: %s", bytes_, hipGetErrorString(e));
         return TM_ENOMEM;
     }
-    for (const Slot& v : slots_) {
-        void* p = base_ + v.at;
-        std::memcpy(v.p, &p, sizeof(p));
+    for (int i = 0; i < n_; ++i) {
+        void* p = base_ + slots_[i].at;
+        std::memcpy(slots_[i].p, &p, sizeof(p));
     }
     return TM_OK;
 }

@@ -205,3 +205,54 @@ def test_product_does_not_import_oracle():
             if f.endswith((".py", ".hip", ".h", ".cpp")):
                 src = open(os.path.join(dirpath, f)).read()
                 assert "import oracle" not in src and "from oracle" not in src, f
+
+
+SCRATCH = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <new>
+#include "tm_internal.h"
+static bool strict = false;
+void* operator new(size_t n) {
+    if (strict) { std::puts("heap allocation"); std::exit(1); }
+    if (void* p = std::malloc(n)) return p;
+    throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
+int main() {
+    strict = true;
+    tmlib::Scratch mem;
+    float* p[15];
+    for (auto& q : p) mem.add(q, 1000);
+    for (auto& q : p) if (q) { std::puts("address before the allocation"); return 1; }
+    if (mem.release(nullptr, TM_OK) != TM_OK) { std::puts("release of nothing"); return 1; }
+    strict = false;
+    tmlib::Scratch over;
+    float* q[25];
+    for (auto& v : q) over.add(v, 1);
+    if (over.allocate(nullptr) != TM_EUNSUPPORTED) { std::puts("25 arrays"); return 1; }
+    std::puts("ok");
+}
+"""
+
+
+def test_scratch_of_a_call_does_not_throw(tmp_path):
+    """Nothing throws across the ABI: the list of a call's scratch arrays takes
+    no memory from the heap (15 arrays, the most that a call has, and more than
+    there is room for)."""
+    import shutil
+    import subprocess
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not found")
+    csrc = os.path.join(ROOT, "paper_2111_07347_amd", "csrc")
+    src, exe = tmp_path / "scratch.hip", tmp_path / "scratch"
+    src.write_text(SCRATCH)
+    r = subprocess.run([hipcc, "-std=c++17", "-O1", "--offload-host-only", f"-I{csrc}",
+                        f"-I{os.path.join(ROOT, 'include')}", str(src),
+                        os.path.join(csrc, "tm_runtime.hip"), "-o", str(exe)],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
