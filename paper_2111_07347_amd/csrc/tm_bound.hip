@@ -1015,8 +1015,7 @@ int tmlib::search_top(const tm_library* lib, const float* polar, const double* n
         int r = bound_match(lib, polar + b0 * pattern, norms + b0, nb, N, 0.0, nullptr, top_template + o,
                             top_angle + o, top_score + o, compact, s);
         if (r == TM_ENOMEM) {
-            (void)hipGetLastError();             // no scratch: the plain scan needs none
-            tmlib::clear_error();
+            tmlib::clear_error();                // no scratch: the plain scan needs none
             r = launch_match(lib, polar + b0 * pattern, norms + b0, nb, N, top_template + o, top_angle + o,
                              top_score + o, nullptr, nullptr, nullptr, 0, nullptr, nullptr, compact, s);
         }

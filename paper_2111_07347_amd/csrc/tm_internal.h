@@ -42,7 +42,8 @@ public:
         ++n_;
         bytes_ += (std::max<size_t>(n, 1) * sizeof(T) + 255) / 256 * 256;
     }
-    // TM_ENOMEM with a message when there is no such memory.
+    // TM_ENOMEM with a message when there is no such memory (the runtime's
+    // last error is cleared: launches after it check theirs).
     int allocate(hipStream_t s);
     // Gives the memory back behind the work on s; r if it is an error, else
     // the status of this call.

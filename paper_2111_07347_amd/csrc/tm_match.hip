@@ -551,8 +551,7 @@ int tmlib::launch_match(const tm_library* lib, const float* polar, const double*
         mem.add(out_s, rows);
         mem.add(out_q, rows);
         if (mem.allocate(s) != TM_OK) {
-            (void)hipGetLastError();             // no scratch: one workgroup per pattern needs none
-            tmlib::clear_error();
+            tmlib::clear_error();                // no scratch: one workgroup per pattern needs none
             parts = 1;
             out_t = top_template;
             out_s = top_angle;
@@ -723,8 +722,7 @@ int tmlib::match_batch_impl(const tm_library* lib, const float* polar, const dou
         r = tmlib::search_items(lib, polar, norms, B, N, items, n_items, top_template, top_angle,
                                 top_score, compact, s);
         if (r == TM_ENOMEM) {
-            (void)hipGetLastError();             // no scratch: the scan of the lists needs none
-            tmlib::clear_error();
+            tmlib::clear_error();                // no scratch: the scan of the lists needs none
             r = TM_OK;
             scan = true;
         }

@@ -33,6 +33,7 @@ int Scratch::allocate(hipStream_t s) {
     hipError_t e = hipMallocAsync(reinterpret_cast<void**>(&base_), std::max<size_t>(bytes_, 256), s);
     if (e != hipSuccess) {
         base_ = nullptr;
+        (void)hipGetLastError();
         set_error("hipMallocAsync(%zu bytes) failed: %s", bytes_, hipGetErrorString(e));
         return TM_ENOMEM;
     }

@@ -212,6 +212,10 @@ SCRATCH = r"""
 #include <cstdlib>
 #include <new>
 #include "tm_internal.h"
+// a runtime out of device memory
+static hipError_t last = hipSuccess;
+extern "C" hipError_t hipMallocAsync(void** p, size_t, hipStream_t) { *p = nullptr; return last = hipErrorOutOfMemory; }
+extern "C" hipError_t hipGetLastError(void) { hipError_t e = last; last = hipSuccess; return e; }
 static bool strict = false;
 void* operator new(size_t n) {
     if (strict) { std::puts("heap allocation"); std::exit(1); }
@@ -232,6 +236,8 @@ int main() {
     float* q[25];
     for (auto& v : q) over.add(v, 1);
     if (over.allocate(nullptr) != TM_EUNSUPPORTED) { std::puts("25 arrays"); return 1; }
+    if (mem.allocate(nullptr) != TM_ENOMEM || p[0]) { std::puts("no memory"); return 1; }
+    if (last != hipSuccess) { std::puts("the error is left to the next launch"); return 1; }
     std::puts("ok");
 }
 """
@@ -240,7 +246,8 @@ int main() {
 def test_scratch_of_a_call_does_not_throw(tmp_path):
     """Nothing throws across the ABI: the list of a call's scratch arrays takes
     no memory from the heap (15 arrays, the most that a call has, and more than
-    there is room for)."""
+    there is room for). An allocation that fails leaves no error behind for the
+    launch after it to report."""
     import shutil
     import subprocess
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
