@@ -118,7 +118,9 @@ enum {
 };
 
 /* Options of tm_match_batch. A NULL options pointer (or all fields zero)
- * means the plain float32 path: every template scored exactly.
+ * means the plain float32 path: the exact top-N over all templates, scored one
+ * and all or, with the same rows, left out where an upper bound of the score
+ * rules them out (below).
  *   prefilter_keep    fraction f of base templates kept by the azimuthal
  *                     pre-filter (Section 2.2, Fig. 3), 0 = no pre-filter;
  *                     the kept ceil(f*T) base templates (and their mirrors)
@@ -136,24 +138,30 @@ enum {
  *                     and score exactly every template whose bound reaches
  *                     the N-th best exact score: the same top-N as the plain
  *                     path, usually after scoring a small fraction of the
- *                     library exactly. Exclusive with the pre-filter. The
- *                     plain path and the rescoring of a pre-filter use the
- *                     same bounds where that is faster (no per-template
- *                     outputs asked for, stream not being captured, scratch
- *                     to be had): same results.
+ *                     library exactly. Exclusive with the pre-filter.
+ *                     Where that is faster the library takes another of
+ *                     these ways to the same rows: the plain path and the
+ *                     rescoring of a pre-filter use the bounds (unless
+ *                     per-template outputs are asked for), and a certified
+ *                     TM_COARSE_FFT call without n_rescored takes the plain
+ *                     path. Not while the stream is captured, nor without
+ *                     the scratch for it.
  *   rescore_policy    with a coarse scorer: TM_RESCORE_CERTIFIED (default)
  *                     or TM_RESCORE_KEEP.
  *   rescore_keep      TM_RESCORE_KEEP: fraction of the T' templates rescored
  *                     (those with the best coarse scores, ties to the lower
  *                     index). TM_RESCORE_CERTIFIED: largest fraction of T'
  *                     rescored from the candidate list (0 = 0.1); a pattern
- *                     whose certified set is larger is scored in full.
+ *                     whose certified set is larger is scored in full. It
+ *                     changes no row, and has no effect on a call that goes
+ *                     another way (see n_rescored).
  *   n_rescored        optional device [B] int32 output: templates scored
- *                     exactly per pattern (T' for a full scan), or NULL. With
- *                     TM_COARSE_BOUND and NULL the library may reach the same
- *                     top-N by other passes that form no such set (finer
- *                     windows for the templates in question); rescore_keep
- *                     then has no effect.
+ *                     exactly per pattern (T' for a full scan), or NULL. A
+ *                     certified call with NULL may reach the same top-N by
+ *                     passes that form no such set (TM_COARSE_BOUND: finer
+ *                     windows for the templates in question; TM_COARSE_FFT:
+ *                     the plain path, without the Fourier kernels); one that
+ *                     asks for the numbers runs the coarse scorer it names.
  *   compact_rows      0: polar is [B, R, n_theta]; 1: polar holds only the
  *                     library's touched rows in increasing order,
  *                     [B, n_rows, n_theta] (tm_polar_transform_rows with the
@@ -341,7 +349,8 @@ int tm_mask_from_mean(const void* patterns, tm_dtype dtype, int32_t B, int32_t H
  *   profiles     device, [R, B] float32 azimuthal profiles; required only
  *                when opts->prefilter_keep > 0, else may be NULL.
  *                With opts->coarse = TM_COARSE_FFT (certified policy), the
- *                result equals the plain path's top-N: every template whose
+ *                result equals the plain path's top-N: where the Fourier
+ *                kernels run (see tm_match_opts), every template whose
  *                approximate score, widened by tm_fft_error_bound(), could
  *                reach the N-th best exact score is rescored exactly.
  *   B            >= 0 (0 is a no-op).
@@ -355,8 +364,11 @@ int tm_mask_from_mean(const void* patterns, tm_dtype dtype, int32_t B, int32_t H
  *                best_score and best_angle must be both NULL or both set,
  *                and are only available without pre-filter or coarse
  *                scorer.
- * Scratch comes from the stream-ordered allocator; the plain path does without
- * where there is none (at most about 4 GiB of bounds at a time).
+ * Scratch comes from the stream-ordered allocator. The plain path takes up to
+ * B x T' x 4 bytes for a large library, at most about 4 GiB at a time, and does
+ * without where there is none. Freed scratch stays in the device's default
+ * memory pool for the next call (the library lifts its release threshold);
+ * hipMemPoolTrimTo gives it back.
  * Errors: TM_EINVAL, TM_EUNSUPPORTED (unknown options), TM_ENOMEM, TM_EHIP,
  *         TM_ENODEV. */
 int tm_match_batch(const tm_library* lib, const float* polar, const double* norms,

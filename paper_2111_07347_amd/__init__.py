@@ -382,7 +382,9 @@ def match_batch(lib: Library, polar, norms, N: int, profiles=None, prefilter_kee
     best_angle [B,T'] i16). coarse="fft" scores every template through the
     Fourier route first and rescores candidates exactly (rescore="certified"
     or "keep" with rescore_keep); n_rescored, a [B] int32 device tensor, if
-    given receives the number of templates scored exactly per pattern."""
+    given receives the number of templates scored exactly per pattern. A
+    certified call without n_rescored may reach the same rows another way
+    (coarse="fft": the plain path)."""
     torch = _torch()
     B = polar.shape[0]
     compact = _layout(lib, polar)
