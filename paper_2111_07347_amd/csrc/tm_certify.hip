@@ -251,8 +251,8 @@ merge_first(const int32_t* __restrict__ full, int B, const double* __restrict__ 
 // Split tasks come first, so the longest work starts first.
 constexpr int kPlanThreads = 1024;
 constexpr int kSlotBudget = 2048;        // partial lists per launch: as many fill the chip, and each
-                                         //   stages the rows again (1024 patterns, all scanned in
-                                         //   full, 2000 FCC templates: 1.13 ms with 16384, 0.86)
+constexpr int kSlotBudgetLong = 16384;   //   stages the rows again; finer where the scan of a pattern
+constexpr int64_t kLongScan = 500000;    //   takes so many vector instructions (see slot_budget)
 constexpr int kChunkCand = 512;          // candidate entries per task
 constexpr int kChunkFull = 256;          // groups per task in a full scan, where staging the
 constexpr int kChunkFullSmall = 64;      //   rows takes long or not
@@ -517,14 +517,23 @@ map_columns(int32_t* __restrict__ idx, size_t n, const int32_t* __restrict__ map
     if (i < n && idx[i] >= 0) idx[i] = map[idx[i]];
 }
 
+// Partial lists of a split launch. 1024 patterns, all scanned in full, 2000 FCC
+// templates (246 thousand instructions): 1.13 ms with 16384, 0.86 with 2048;
+// most of 2362 patterns, 7596 orthorhombic templates on 90 columns (2.1 million):
+// 9.6 ms, 10.6.
+int slot_budget(const tm_library* lib) {
+    const int64_t work = lib->n_records * (1 + lib->group * tmlib::slots_for(lib->n_theta));
+    return work >= kLongScan ? kSlotBudgetLong : kSlotBudget;
+}
+
 // Scratch of a split launch: its plan and the partial lists.
 struct SplitScratch {
     int4 *tasks, *merges;
     int32_t *meta, *pt, *ps;
     float* pq;
     int slots;
-    SplitScratch(tmlib::Scratch& m, int32_t B, int32_t N, int64_t most_tasks)
-        : slots(static_cast<int>(std::min<int64_t>(kSlotBudget, most_tasks))) {
+    SplitScratch(tmlib::Scratch& m, const tm_library* lib, int32_t B, int32_t N, int64_t most_tasks)
+        : slots(static_cast<int>(std::min<int64_t>(slot_budget(lib), most_tasks))) {
         const size_t lists = static_cast<size_t>(slots) * N;
         m.add(tasks, static_cast<size_t>(B) + slots);
         m.add(merges, B);
@@ -603,7 +612,7 @@ int tmlib::certified_rescore(const tm_library* lib, const float* polar, const do
     mem.add(cand, static_cast<size_t>(B) * cap);
     mem.add(cnt, B);
     mem.add(full, B);
-    SplitScratch sc(mem, B, N, std::max(most_tasks(B, cap, kChunkCand), most_tasks(B, lib->n_groups, chunk_full(lib))));
+    SplitScratch sc(mem, lib, B, N, std::max(most_tasks(B, cap, kChunkCand), most_tasks(B, lib->n_groups, chunk_full(lib))));
     int r = mem.allocate(s);
     // 1. the n_first best estimates (or of the caller's short list), scored
     // exactly: their N-th best, q_N
@@ -674,7 +683,7 @@ int tmlib::full_scans(const tm_library* lib, const float* polar, const double* n
                       float* top_score, bool compact, hipStream_t s, const int32_t* cand, int32_t n_cand) {
     const int32_t n_items = cand ? n_cand : lib->n_groups;
     tmlib::Scratch mem;
-    SplitScratch sc(mem, B, N, most_tasks(B, n_items, cand ? kChunkCand : chunk_full(lib)));
+    SplitScratch sc(mem, lib, B, N, most_tasks(B, n_items, cand ? kChunkCand : chunk_full(lib)));
     int r = mem.allocate(s);
     if (!r)
         r = split_pass(lib, polar, norms, B, N, full, true, cand, nullptr, n_items, sc,

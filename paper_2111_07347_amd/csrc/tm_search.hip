@@ -76,7 +76,6 @@ constexpr int kSeedPicks = 32;           // columns of Qc that seed the search, 
 constexpr int kMaxSeeds = 256;           //   and at the most
 constexpr int kPend = 32;                // columns of Qc per wave and round
 constexpr int kSel = 256;                // listed columns per round (kAll, kItems)
-constexpr int kSeedColumns = 64;         //   and of the seeds (where many have alike bounds)
 constexpr uint32_t kDone = 0xffffu;      // a bound that is dealt with
 constexpr double kSparse = 24;           // most records per template of a sparse library
 constexpr double kItemsSparse = 150000;  // a list's pixels x shift slots from which a search pays:
@@ -835,7 +834,6 @@ search_kernel(const SearchArgs a) {
 #pragma unroll 1
         for (bool seed = !flat;; seed = false) {
             const int want = seed ? n_seed_scored : kBatch;
-            const int most = seed ? max(kSeedColumns, want) : kSel;
             const float q = C.q;
             __syncthreads();
             if (tid < 64) C.hist[tid] = 0;
@@ -898,13 +896,13 @@ search_kernel(const SearchArgs a) {
                 const uint32_t u = i < n_ub ? ub[i] : kDone;
                 const bool take = u != kDone && h2f(u) >= q && bin(u) >= cut;
                 const int at = place(&C.work, take, lane);
-                if (take && at < most) {
+                if (take && at < kSel) {
                     L.pend[at] = static_cast<uint16_t>(i);
                     if (!seed) ub[i] = static_cast<uint16_t>(kDone);
                 }
             }
             __syncthreads();
-            const int ns = min(C.work, most);
+            const int ns = min(C.work, kSel);
 #pragma unroll 1
             for (int j0 = wave * G; j0 < ns; j0 += NW * G) {
                 const int j = j0 + lane / W;
