@@ -95,7 +95,7 @@ int32_t split_parts(int32_t B, int64_t work, int32_t n_groups, int nw, size_t ld
     else if (B <= kCus)
         grid = w >= 100000 ? 4 * kCus : B;
     else
-        grid = B <= kCus * 7 / 4 ? 3 * B : B;
+        grid = B <= kCus + kCus / 2 ? 3 * B : B;
     const int64_t most = std::min(n_groups / (kPartGroups * nw * (1 + whole)), kMaxParts);
     return static_cast<int32_t>(std::max<int64_t>(1, std::min(grid / B, most)));
 }
