@@ -166,7 +166,7 @@ def time_steps(step, steps, warmup, n_marks=3):
 # Sources that define each kernel whose traffic the benchmark reports.
 KERNEL_SOURCES = {
     "match_kernel": ("tm_match.hip", "tm_library.hip", "tm_topn.h"),
-    "bound_kernel": ("tm_bound.hip",),
+    "bound_kernel": ("tm_bound.hip", "tm_window.h"),
     "polar_kernel": ("tm_polar.hip",),
     "fft_": ("tm_fft.hip",),
 }

@@ -124,7 +124,15 @@ constexpr int64_t kBoundRecords = 131072;  // records from which a search of a d
 constexpr int32_t kSearchChunk = 65536;    // patterns of a plain path's search at a time, and
 constexpr size_t kSearchScratch = size_t(4) << 30;   // the bytes of their bounds
 constexpr int kFillGrid = 512;             // workgroups that fill the chip (two per CU)
-constexpr int kRefineBatch = 128;          // largest batch of a dense library that is refined,
+// Few patterns of a dense library leave the certified passes' launches short of
+// work; their refinement takes one (us, refined, certified; orthorhombic, 256 x
+// 256: 20 000 templates, one pattern 233, 432; 32: 427, 501; 128: 646, 612; 8000
+// on 180 columns, 32: 305, 319; 128: 864, 365). Crowded templates have too many
+// patterns without a clear best one for it, unless the batch is so small that
+// the passes are all launches (128 x 128, 11 600 templates, 3 patterns: 406,
+// 1054; 20 000, one: 1415, 930; 32: 2307, 1598; 128: 6549, 3790).
+constexpr int kRefineBatch = 48;           // largest batch of a dense library that is refined,
+constexpr int kRefineCrowded = 8;          //   the same of a crowded one,
 constexpr int kRefineTemplates = 8192;     //   its least templates
 constexpr int64_t kRefineSpots = 24;       //   and pixels per template
 // Columns of a polar row: with up to two per lane a scan of a dense library is
@@ -944,7 +952,8 @@ int tmlib::bound_match(const tm_library* lib, const float* polar, const double* 
     if (!n_rescored && searches_all(lib, B))
         return tmlib::search_all(lib, polar, norms, B, N, top_template, top_angle, top_score, compact, s);
     // the certified rescoring's list holds one workgroup's lanes
-    const bool refine = lib->search && !n_rescored && B <= kRefineBatch && Tp >= kRefineTemplates &&
+    const bool refine = lib->search && !n_rescored && B <= (crowded(lib) ? kRefineCrowded : kRefineBatch) &&
+                        Tp >= kRefineTemplates &&
                         lib->n_spots >= kRefineSpots * Tp &&
                         lib->n_theta > kRefineColumns[0] && lib->n_theta <= kRefineColumns[1];
     const int split = refine ? bound_split(lib, B) : 1;

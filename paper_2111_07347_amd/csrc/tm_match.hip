@@ -104,18 +104,15 @@ int32_t split_parts(int32_t B, int64_t work, int32_t n_groups, int nw, size_t ld
 // is faster than the Fourier route (searched or scanned), and records x patterns
 // below which it is for any library: the route takes a dozen launches. Of a dense
 // library it depends on the patterns: without a clear best template they are
-// scanned in full, which takes twice the route's time. That becomes common
-// where a template has more than a pixel per touched row, so that a quarter
-// turn of nearly every row holds a spot (orthorhombic templates of 76 pixels,
-// 256 patterns, us by plain path and route: 53 rows, 28 000 templates 11404,
-// 4596, 8000: 3388, 1470; 64 rows: 6325, 4599 and 1267, 1514; 76: 1685, 5212 and
-// 897, 1682; 95: 528, 5365 and 350, 1775): up to kRowPixels per row, or up to so
-// many patterns x templates x columns that the route's launches count (37 778
-// templates on 720 columns, one pattern: 4.9 ms, 6.1).
+// scanned in full, which takes twice the route's time (orthorhombic templates of
+// 76 pixels, 256 patterns, us by plain path and route: 53 rows, 28 000 templates
+// 11404, 4596, 8000: 3388, 1470; 64 rows: 6325, 4599 and 1267, 1514; 76: 1685,
+// 5212 and 897, 1682; 95: 528, 5365 and 350, 1775): not where templates are
+// crowded, but for so few patterns x templates x columns that the route's
+// launches count (37 778 templates on 720 columns, one pattern: 4.9 ms, 6.1).
 constexpr int64_t kSparseRecords = 8192;
 constexpr int64_t kSparseWork = 3000000;
 constexpr int64_t kScanWork = 1500000;
-constexpr double kRowPixels = 1.08;
 constexpr int64_t kDenseWork = 150000000;
 
 // One union pixel of a group: LDS float offset within the band, then one
@@ -681,7 +678,7 @@ int tmlib::match_batch_impl(const tm_library* lib, const float* polar, const dou
     if (coarse == TM_COARSE_FFT && policy == TM_RESCORE_CERTIFIED && !n_rescored && may_allocate &&
         ((lib->sr_all ? lib->n_records >= kSparseRecords || static_cast<int64_t>(B) * lib->n_records >= kSparseWork
                       : tmlib::search_pays(lib, B) &&
-                            (static_cast<double>(lib->n_spots) <= kRowPixels * lib->n_rows * lib->Tp ||
+                            (!tmlib::crowded(lib) ||
                              static_cast<int64_t>(B) * lib->Tp <= kDenseWork / lib->n_theta)) ||
          static_cast<int64_t>(B) * lib->n_records < kScanWork))
         coarse = TM_COARSE_NONE;

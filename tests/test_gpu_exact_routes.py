@@ -32,22 +32,26 @@ def _library(tm, n_theta, T, max_spots, **kw):
 
 # widths at the ends of what is refined (129 to 384 columns), with and without
 # 8 | n_theta; batches of one workgroup per pattern and of several, and the
-# first that is not refined; templates below and above the least number
-@pytest.mark.parametrize("n_theta,T,max_spots,refined", [
-    (129, 4200, 90, True), (180, 4200, 80, True), (361, 4100, 90, True), (384, 4500, 70, True),
-    (385, 4200, 90, False), (360, 1500, 90, False)])
-def test_dense_libraries(tm, n_theta, T, max_spots, refined):
+# first that is not refined (49; 9 of crowded templates, those with more than
+# about a pixel per row); templates below and above the least number
+@pytest.mark.parametrize("n_theta,rows,T,max_spots,refined", [
+    (129, 60, 4200, 60, True), (180, 60, 4200, 70, True), (361, 64, 4100, 70, True),
+    (384, 60, 4500, 70, True), (385, 60, 4200, 70, False), (360, 60, 1500, 70, False),
+    (180, 34, 4200, 80, False)])
+def test_dense_libraries(tm, n_theta, rows, T, max_spots, refined):
     import torch
-    lib, lib_np, grid = _library(tm, n_theta, T, max_spots)
-    info = lib.info()
-    # dense, and of as many templates as the route takes
-    assert info["n_spots"] > 24 * info["n_templates_total"]
-    assert (info["n_templates_total"] >= 8192 and 128 < n_theta <= 384) == refined
-    for B in (1, 3, 40, 128, 129):
-        print("[case] dense", n_theta, T, max_spots, "B", B, flush=True)
-        x = torch.from_numpy(_patterns(lib_np, PX, R, B, seed=B)).cuda()
-        for rows in (lib, None):
-            polar, norms, _ = tm.polar_transform(x, grid, lib=rows)
+    lib_np = small_library(T, seed=n_theta + T, max_spots=max_spots, g_min=0.08, g_max=1.1)
+    px = (rows - 4) / 1.2
+    grid = tm.PolarGrid(R=rows, n_theta=n_theta, cx=62.0, cy=64.0)
+    lib = tm.Library(lib_np["kx"], lib_np["ky"], lib_np["intensity"], lib_np["offsets"], px, grid)
+    pixels = lib.info()["n_spots"] / lib.n_total
+    assert pixels > 24                           # dense, and as the route wants them or not
+    assert refined == (lib.n_total >= 8192 and 128 < n_theta <= 384 and pixels < 1.08 * lib.rows()[0])
+    for B in (1, 3, 8, 9, 40, 48, 49, 129):
+        print("[case] dense", n_theta, rows, T, max_spots, "B", B, flush=True)
+        x = torch.from_numpy(_patterns(lib_np, px, rows, B, seed=B, H=128, W=124)).cuda()
+        for touched in (lib, None):
+            polar, norms, _ = tm.polar_transform(x, grid, lib=touched)
             if B > 4:
                 norms[4] = float("nan")
                 polar[4, 0, 0] = float("nan")
