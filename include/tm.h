@@ -679,8 +679,9 @@ int tm_fft_scores(const tm_library* lib, const float* polar, const double* norms
  *   B             >= 0 (0 is a no-op).
  *   bound_out     device, [B, T'] float32, written. A pattern with a
  *                 non-finite norm gets 0 (tm_match_batch flags it); one whose
- *                 largest |P| over the touched rows is below 2^-100, or whose
- *                 1 / ||P|| is above 2^127, gets +infinity.
+ *                 largest |P| over the touched rows is below 2^-100 (or
+ *                 outside [2^-40, 2^100] ||P||), or whose 1 / ||P|| is above
+ *                 2^127 or below 2^-125, gets +infinity.
  * Errors: TM_EINVAL, TM_EUNSUPPORTED, TM_EHIP, TM_ENODEV. */
 int tm_bound_scores(const tm_library* lib, const float* polar, const double* norms, int32_t B,
                     int32_t compact_rows, float* bound_out, void* hip_stream);

@@ -527,9 +527,9 @@ search_kernel(const SearchArgs a) {
         if (tid == 0) a.give[b * a.parts + part] = 1;
         return;
     }
-    const tmlib::WindowScale ws = tmlib::window_scale(A);
-    const float scale = ws.image;
+    float scale = 1.0f;
     if (!flat) {
+        scale = tmlib::window_scale(A).image;
         // ---- the window image, row by row: clamped, scaled, rounded-up
         // float16 values of a row and a halo of H columns in rb, maxima of its
         // aligned blocks of o columns in bm; lane l takes the o columns from
@@ -621,12 +621,10 @@ search_kernel(const SearchArgs a) {
     }
     __syncthreads();
     const float Ahat = h2f(f16_up(A * scale));
-    // bound = sum to_p invP_up, to_p = out_scale dfac (1 + 2^-18) (out_scale a
-    // power of 2): the first product is at least the plain path's sum, for the
-    // last factor more than restores its rounding, and the second at least its
-    // score, rounding being monotone (also where 1 / ||P|| is subnormal)
-    const float invUp = tmlib::inverse_up(pn);
-    const float to_p = ws.undo * (a.dfac * (1.0f + 0x1p-18f));
+    // bound = sum to_q, to_q = out_scale dfac invP_up (1 + 2^-18), out_scale the
+    // inverse of the scales, a power of 2: the last factor more than restores
+    // the roundings (of normal numbers: see no_window_bounds)
+    const float to_q = a.dfac * tmlib::inverse_up(pn) * (1.0f + 0x1p-18f) / (scale * static_cast<float>(1 << kWeightExp));
     if (tid == 0) {
         C.cnt = flat && part == 0 ? N : 0;
         C.q = -INFINITY;
@@ -641,7 +639,7 @@ search_kernel(const SearchArgs a) {
     // listed with their windows (seed: with the best window alone, whatever q).
     auto evaluate = [&](int col, bool seed) {
         const int t = col >= 0 ? a.tid[col] : -1;
-        const float u = (window_sum(a, img, col, Ahat, lane) * to_p) * invUp;
+        const float u = window_sum(a, img, col, Ahat, lane) * to_q;
         float U = u;
 #pragma unroll
         for (int d = W / 2; d >= 1; d >>= 1) U = fmaxf(U, __shfl_xor(U, d, 64));
@@ -815,7 +813,7 @@ search_kernel(const SearchArgs a) {
         if constexpr (KIND == kAll) {
 #pragma unroll 1
             for (int c = wave; c * 64 < n_ub; c += NW) {
-                const float u = (max_window(a, img, first + c, Ahat, lane) * to_p) * invUp;
+                const float u = max_window(a, img, first + c, Ahat, lane) * to_q;
                 ub[c * 64 + lane] =
                     static_cast<uint16_t>(a.tid[(first + c) * 64 + lane] >= 0 ? f16_up(u) : kDone);
             }
@@ -823,7 +821,7 @@ search_kernel(const SearchArgs a) {
 #pragma unroll 1
             for (int j0 = wave * G; j0 < n_ub; j0 += NW * G) {
                 const int j = j0 + lane / W;
-                float U = (window_sum(a, img, j < n_ub ? column(j) : -1, Ahat, lane) * to_p) * invUp;
+                float U = window_sum(a, img, j < n_ub ? column(j) : -1, Ahat, lane) * to_q;
 #pragma unroll
                 for (int d = W / 2; d >= 1; d >>= 1) U = fmaxf(U, __shfl_xor(U, d, 64));
                 if (j < n_ub && (lane & (W - 1)) == 0) ub[j] = static_cast<uint16_t>(f16_up(U));

@@ -39,11 +39,14 @@ __host__ __device__ __forceinline__ float inverse_up(double pn) {
     return static_cast<double>(f) < ip ? nextafterf(f, INFINITY) : f;
 }
 
-// Whether a pattern with intensities has no window bounds: too faint, or
-// 1 / ||P|| (rounded either way) at the end of the range, past which its
-// scores are infinite.
+// Whether a pattern with intensities has no window bounds: too faint, 1 / ||P||
+// (rounded either way, 0 for no norm) at the end of the range, past which its
+// scores are infinite, or subnormal, or a norm that is not its own and so far
+// off that the product of the bounds' factors (about A / ||P|| / 2^24) could
+// leave the normal numbers.
 __host__ __device__ __forceinline__ bool no_window_bounds(float A, float inv) {
-    return A > 0.0f && (A < kFaint || inv > 0x1p127f);
+    return A > 0.0f && (A < kFaint || inv > 0x1p127f ||
+                        (inv > 0.0f && (inv < 0x1p-125f || !(A * inv >= 0x1p-40f && A * inv <= 0x1p100f))));
 }
 
 __host__ __device__ __forceinline__ float h2f(uint32_t bits16) {

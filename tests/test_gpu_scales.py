@@ -63,3 +63,23 @@ def test_rows_at_every_scale(tm, T, max_spots, n_theta, Bs):
             assert bool((b >= best).all())
     lib.free()
 
+
+
+# norms that are not the patterns' own, either side of where the window bounds
+# stop
+@pytest.mark.parametrize("k", (-110, -90, 30, 45, 110))
+def test_rows_with_norms_of_another_scale(tm, k):
+    import torch
+    R, T, B = 34, 2500, 9
+    lib_np = small_library(T, seed=T, max_spots=8, g_min=0.08, g_max=1.1)
+    grid = tm.PolarGrid(R=R, n_theta=360, cx=33.0, cy=35.0)
+    lib = tm.Library(lib_np["kx"], lib_np["ky"], lib_np["intensity"], lib_np["offsets"],
+                     (R - 4) / 1.2, grid)
+    x = torch.from_numpy(_patterns(lib_np, (R - 4) / 1.2, R, B, seed=B)).cuda()
+    polar, norms, _ = tm.polar_transform(x, grid, lib=lib)
+    norms = norms * 2.0 ** k
+    ref = tm.match_batch(lib, polar, norms, 5, with_best=True)
+    assert _same(tm.match_batch(lib, polar, norms, 5), ref[:3])
+    assert _same(tm.match_batch(lib, polar, norms, 5, coarse="bound"), ref[:3])
+    assert bool((tm.bound_scores(lib, polar, norms) >= ref[3]).all())
+    lib.free()

@@ -28,7 +28,7 @@ int main() {
             check(static_cast<double>(inv) * (static_cast<double>(A) * 8.0) >= 1.0, "inverse rounded down", A);
             if (no_window_bounds(A, inv)) {
                 ++without;
-                check(e < -90, "no bounds for an ordinary pattern", A);
+                check(e < -90 || e >= 121, "no bounds for an ordinary pattern", A);
                 continue;
             }
             ++with;
@@ -43,6 +43,9 @@ int main() {
     check(with > 0 && without > 0, "both kinds", 0.0f);
     for (float x = 1e-9f; x < 70000.0f; x *= 1.0009f) check(h2f(f16_up(x)) >= x, "float16 rounded down", x);
     check(no_window_bounds(1.0f, INFINITY), "1 / norm past the range", 1.0f);
+    check(no_window_bounds(0x1p-90f, 0x1p-90f), "a norm far above the pattern's", 0x1p-90f);
+    check(no_window_bounds(0x1p60f, 0x1p60f), "a norm far below the pattern's", 0x1p60f);
+    check(!no_window_bounds(1.0f, 0.0f), "no norm", 1.0f);
     check(!no_window_bounds(0.0f, 0.0f), "a blank pattern needs no scan", 0.0f);
     check(inverse_up(0.0) == 0.0f && inverse_up(-1.0) == 0.0f, "no norm", 0.0f);
     std::puts("ok");
