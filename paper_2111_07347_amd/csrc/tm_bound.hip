@@ -87,9 +87,11 @@
 //   * a chunk's bounds leave as one coalesced 256-byte store, in chunk-slot
 //     order (the library's slot -> template map goes with them).
 //
-// Bound: vector issue (5.7 instructions per record, one per clock and CU).
-// 16 384 patterns, 20 000 templates of 76 spots on average: 10.8 ms; 11.9 ms
-// with two 4-byte reads per record, which kept the LDS busy 96 % of the time.
+// Bound: vector issue (5.7 instructions per record, one per clock and CU: 84 %
+// of the clocks). 16 384 patterns, 20 000 templates of 76 spots on average:
+// 10.4 to 10.8 ms; 11.9 ms with two 4-byte reads per record, which took 4.7
+// clocks (8 bytes: 2.65) and twice the cycles of bank conflicts (2.04e9, now
+// 1.03e9, beside 9.4e8 reads).
 #include <algorithm>
 #include <array>
 #include <cmath>

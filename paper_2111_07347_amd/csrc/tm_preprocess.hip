@@ -29,7 +29,7 @@
 // radius r takes 16 + 2 r products per output, against 2 r + 1 of the filter
 // alone; the vector units' share is the staging.
 // Measured (1024 uint16 patterns of 256 x 256, sigma 1 / 6 / 1, all steps):
-// 478 us, 60 % of it matrix-core issue, against 1061 us of separate row and
+// 478 us, 37 % of it matrix-core issue, against 1061 us of separate row and
 // column passes for the difference and the blur on the vector units (ten image
 // sizes of HBM traffic). Strips of 64 columns and 8 waves take 453 us, but
 // their rings exceed the LDS at the largest reach.

@@ -37,10 +37,10 @@
 // the latency of short dependent phases, hidden by 16 to 32 waves per CU.
 // Measured (256 x 256 patterns, top-5, search alone, before -> now; before:
 // the plain scan, or the pre-filter's candidate scan): 16384 patterns x 2000
-// FCC templates 8.3 -> 2.1 ms; 256 patterns 0.29 -> 0.15 ms; 1024 patterns x
+// FCC templates 8.3 -> 2.1 ms; 256 patterns 0.29 -> 0.14 ms; 1024 patterns x
 // 20000 orthorhombic templates, BF16 pre-filter keeping a tenth, candidate
-// pass 8.5 -> 1.4 ms; one pattern x 20000 templates against the certified
-// passes after the bound kernel 0.42 -> 0.21 ms.
+// pass 8.5 -> 1.7 ms; one pattern x 20000 templates against the certified
+// passes after the bound kernel 0.42 -> 0.13 ms.
 //
 // Rigour in finite precision is that of tm_bound.hip: image and weights
 // rounded up to float16 with exact products, float32 sums widened by 1 / (1 -
