@@ -123,6 +123,10 @@ constexpr int64_t kBoundRecords = 131072;  // records from which a search of a d
                                            //   (766 orthorhombic templates, 483 patterns: 1.8 ms
                                            //   scanned, 2.1 searched; 999, 52 patterns, 720 columns:
                                            //   1.0 and 2.2; 3000, 512 patterns: 0.9 searched)
+constexpr int64_t kBoundAlways = 1000000;  // and from which it always does
+constexpr int64_t kRefineRecords = 450000; // least records of a crowded one that is refined rather
+                                           //   than scanned (8 patterns, 5000 templates on 180
+                                           //   columns: 0.94, 0.38 ms; 8000: 0.40, 0.54)
 constexpr int32_t kSearchChunk = 65536;    // patterns of a plain path's search at a time, and
 constexpr size_t kSearchScratch = size_t(4) << 30;   // the bytes of their bounds
 constexpr int kFillGrid = 512;             // workgroups that fill the chip (two per CU)
@@ -894,6 +898,12 @@ bool searches_all(const tm_library* L, int32_t B) {
     return L->sr_all && !loose && !(many && (few_columns || n > kRefineColumns[1]));
 }
 
+// Whether a dense library's bounds are refined (see kRefineBatch).
+bool refines(const tm_library* L, int32_t B) {
+    return L->search && B <= (tmlib::crowded(L) ? kRefineCrowded : kRefineBatch) && L->Tp >= kRefineTemplates &&
+           L->n_spots >= kRefineSpots * L->Tp && L->n_theta > kRefineColumns[0] && L->n_theta <= kRefineColumns[1];
+}
+
 }  // namespace
 
 int tmlib::bound_scores_impl(const tm_library* L, const float* polar, const double* norms,
@@ -954,10 +964,7 @@ int tmlib::bound_match(const tm_library* lib, const float* polar, const double* 
     if (!n_rescored && searches_all(lib, B))
         return tmlib::search_all(lib, polar, norms, B, N, top_template, top_angle, top_score, compact, s);
     // the certified rescoring's list holds one workgroup's lanes
-    const bool refine = lib->search && !n_rescored && B <= (crowded(lib) ? kRefineCrowded : kRefineBatch) &&
-                        Tp >= kRefineTemplates &&
-                        lib->n_spots >= kRefineSpots * Tp &&
-                        lib->n_theta > kRefineColumns[0] && lib->n_theta <= kRefineColumns[1];
+    const bool refine = !n_rescored && refines(lib, B);
     const int split = refine ? bound_split(lib, B) : 1;
     const int n_list = split * bound_waves(lib) * 64;
     const size_t nl = static_cast<size_t>(B) * n_list;
@@ -989,6 +996,10 @@ int tmlib::bound_match(const tm_library* lib, const float* polar, const double* 
     return mem.release(s, r);
 }
 
+bool tmlib::bounds_pay(const tm_library* lib) {
+    return lib->bound && lib->n_records >= kBoundRecords && lib->n_theta > kRefineColumns[0];
+}
+
 // Whether the plain path finds its top-N by the window-bound search. A sparse
 // library's search costs a pattern a fixed part (window image, bounds of all
 // templates, seeds) in a chain of short phases, which few patterns do not
@@ -1004,9 +1015,29 @@ int tmlib::bound_match(const tm_library* lib, const float* polar, const double* 
 // 180 (76 thousand), 512: 182, 203; 2048: 500, 349; 2000 FCC on 90 (77
 // thousand), 4096: 1150, 1388; 6000 (210 thousand), 1024: 893, 1037; 4096: 2965,
 // 2318; 3000 HCP (216 thousand), 512: 408, 609; 1024: 682, 599.
+//
+// A dense library's certified passes are a dozen launches, and patterns without
+// a clear best template, common the more pixels a touched row has per template
+// (see crowded), end in a full scan after them: about 1 ms where there are some,
+// which the scan of all stays below up to some b w, lower the larger the
+// library (of which the bounds leave a smaller part). Orthorhombic templates of 76
+// pixels on 53 rows (1.44 pixels): 3000 on 180 columns (w 2.1 million), 8
+// patterns 195, 747; 256: 1280, 1709; on 360 (4.3 million), 16: 270, 770; 1500 on
+// 720 (5.3 million), 256: 4017, 5627; 8000 on 360 (10.4 million), 16: 563, 1018;
+// 64: 1818, 1579; 62 rows (1.23), 32: 980, 579; 71 rows (1.07), 3000 on 180, 64:
+// 475, 925; 128: 956, 942; 81 rows (0.94), 48: 384, 913; on 360, 32: 473, 399;
+// 64: 839, 406; 95 rows (0.80): 1: 248, 189; 64: 806, 255. Large libraries'
+// scans are no cheaper (20 000 on 180 and 53 rows, 16: 1186, 1347; on 720:
+// 4529, 3031).
 bool tmlib::search_pays(const tm_library* lib, int32_t B) {
-    if (!lib->sr_all) return lib->bound && lib->n_records >= kBoundRecords && lib->n_theta > kRefineColumns[0];
     const double b = B, w = static_cast<double>(lib->n_records) * (1 + lib->group * slots_for(lib->n_theta));
+    if (!lib->sr_all) {
+        if (!bounds_pay(lib) || lib->n_records >= kBoundAlways) return bounds_pay(lib);
+        if (refines(lib, B) && !(crowded(lib) && lib->n_records < kRefineRecords)) return true;
+        const double pixels = static_cast<double>(lib->n_spots) / lib->n_rows / lib->Tp;
+        const double records = static_cast<double>(lib->n_records);
+        return b * w * records >= 2.3e14 * (pixels - 0.8) * (lib->n_theta > kRefineColumns[1] ? 2 : 1);
+    }
     if (lib->n_theta <= 128) return w >= 9e4 && b * w >= 2.2e8 && b * b * w >= 5e10;
     const bool large = w >= 1e5 && lib->n_spots < kManySpots * lib->Tp;
     if (lib->n_theta <= kFewColumns) return b * b * w >= 2.4e10 && (large || (w >= 6e4 && b * w >= 8e7));

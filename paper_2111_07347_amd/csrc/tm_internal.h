@@ -222,6 +222,7 @@ int search_items(const tm_library* lib, const float* polar, const double* norms,
 
 // The plain path's top-N by search: whether that pays for B patterns, and
 // the search (without scratch to be had: the plain scan). Enqueued on s.
+bool bounds_pay(const tm_library* lib);   // a dense library's, for some number of patterns
 bool search_pays(const tm_library* lib, int32_t B);
 int search_top(const tm_library* lib, const float* polar, const double* norms, int32_t B, int32_t N,
                int32_t* top_template, int32_t* top_angle, float* top_score, bool compact,

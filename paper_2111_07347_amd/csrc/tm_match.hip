@@ -102,18 +102,41 @@ int32_t split_parts(int32_t B, int64_t work, int32_t n_groups, int nw, size_t ld
 
 // Records, or records x patterns, of a sparse library from which the plain path
 // is faster than the Fourier route (searched or scanned), and records x patterns
-// below which it is for any library: the route takes a dozen launches. Of a dense
-// library it depends on the patterns: without a clear best template they are
-// scanned in full, which takes twice the route's time (orthorhombic templates of
-// 76 pixels, 256 patterns, us by plain path and route: 53 rows, 28 000 templates
-// 11404, 4596, 8000: 3388, 1470; 64 rows: 6325, 4599 and 1267, 1514; 76: 1685,
-// 5212 and 897, 1682; 95: 528, 5365 and 350, 1775): not where templates are
-// crowded, but for so few patterns x templates x columns that the route's
-// launches count (37 778 templates on 720 columns, one pattern: 4.9 ms, 6.1).
+// below which it is for any library: the route takes a dozen launches.
 constexpr int64_t kSparseRecords = 8192;
 constexpr int64_t kSparseWork = 3000000;
 constexpr int64_t kScanWork = 1500000;
-constexpr int64_t kDenseWork = 150000000;
+
+// Patterns up to which the plain path of a dense library is faster than the
+// Fourier route, which works in tiles of 64 (orthorhombic templates of 76
+// pixels, us by plain path and route, 24 patterns: 3000 on 180 columns 267,
+// 297; on 360, 16 patterns: 270, 419; 8000: 563, 818; on 720: 2022, 2474; 32:
+// 3005, 2493). Beyond, it depends on the patterns: without a clear best
+// template they are scanned in full, which takes twice the route's time (256
+// patterns: 53 rows, 28 000 templates 11404, 4596, 8000: 3388, 1470; 64 rows:
+// 6325, 4599 and 1267, 1514; 76: 1685, 5212 and 897, 1682; 95: 528, 5365 and
+// 350, 1775): not where templates are crowded, nor, with nearly a pixel per row
+// and template, for short scans (3000 templates on 180 columns and 81 rows, 64
+// patterns: 919, 314; 512: 995, 1330; 5000 on 360, 32: 236, 668; 3000 on 180 and
+// 95 rows, 64: 276, 303).
+constexpr int32_t kFewPatterns = 24;
+constexpr double kFourierWork = 4e8;         // patterns x vector instructions of a scan,
+constexpr int64_t kFourierRecords = 300000;  // or records, that are not short
+constexpr double kFourierPixels = 0.9;       // nearly a pixel
+
+// Whether certified rows come sooner from the plain path than from the Fourier
+// kernels.
+bool plain_before_fourier(const tm_library* lib, int32_t B) {
+    const int64_t scan = B * lib->n_records;
+    if (scan < kScanWork) return true;
+    if (lib->sr_all) return lib->n_records >= kSparseRecords || scan >= kSparseWork;
+    if (!tmlib::bounds_pay(lib)) return false;
+    if (B <= kFewPatterns) return true;
+    return !tmlib::crowded(lib) && tmlib::search_pays(lib, B) &&
+           (static_cast<double>(scan) * (1 + lib->group * tmlib::slots_for(lib->n_theta)) >= kFourierWork ||
+            lib->n_records >= kFourierRecords ||
+            static_cast<double>(lib->n_spots) < kFourierPixels * lib->n_rows * lib->Tp);
+}
 
 // One union pixel of a group: LDS float offset within the band, then one
 // weight per group member.
@@ -676,11 +699,7 @@ int tmlib::match_batch_impl(const tm_library* lib, const float* polar, const dou
     // (300 FCC templates, 64 patterns: 212 -> 59 us; 100 orthorhombic ones,
     // 300 patterns, 2e6 records: 218 -> 224, beyond the rule).
     if (coarse == TM_COARSE_FFT && policy == TM_RESCORE_CERTIFIED && !n_rescored && may_allocate &&
-        ((lib->sr_all ? lib->n_records >= kSparseRecords || static_cast<int64_t>(B) * lib->n_records >= kSparseWork
-                      : tmlib::search_pays(lib, B) &&
-                            (!tmlib::crowded(lib) ||
-                             static_cast<int64_t>(B) * lib->Tp <= kDenseWork / lib->n_theta)) ||
-         static_cast<int64_t>(B) * lib->n_records < kScanWork))
+        plain_before_fourier(lib, B))
         coarse = TM_COARSE_NONE;
     if (coarse == TM_COARSE_FFT)
         return tmlib::fft_match(lib, polar, norms, B, N, policy, rescore_keep, n_rescored,

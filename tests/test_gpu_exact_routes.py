@@ -166,16 +166,28 @@ def test_sparse_libraries_by_scan_search_or_certified(tm, n_theta, T, max_spots,
     lib.free()
 
 
-def test_dense_fourier_calls_by_either_route(tm):
-    """Certified Fourier calls without counts: a dense library's take the plain
-    path up to a number of patterns (99 of these), the kernels beyond."""
+# crowded libraries, one with about a pixel per row and template and one with
+# fewer; patterns on either side of the rules that choose between scan, search
+# and, for certified Fourier calls without counts, the Fourier kernels
+@pytest.mark.parametrize("n_theta,rows,T,max_spots", [(180, 34, 4200, 80), (360, 34, 2600, 80),
+                                                      (180, 34, 3900, 51), (180, 60, 2600, 70),
+                                                      (386, 34, 2000, 80)])
+def test_dense_libraries_by_scan_search_or_fourier(tm, n_theta, rows, T, max_spots):
     import torch
-    lib, lib_np, grid = _library(tm, 180, 4200, 80, fft=True)
-    assert lib.info()["n_spots"] > 24 * lib.n_total
-    x = torch.from_numpy(_patterns(lib_np, PX, R, 110, seed=5)).cuda()
-    polar, norms, _ = tm.polar_transform(x, grid, lib=lib)
-    for B in (1, 99, 100, 110):
-        print("[case] dense fourier, B", B, flush=True)
-        p, n = polar[:B], norms[:B]
-        assert same_rows(tm.match_batch(lib, p, n, 5, coarse="fft"), exhaustive(tm, lib, p, n, 5)), B
+    lib_np = small_library(T, seed=n_theta + T, max_spots=max_spots, g_min=0.08, g_max=1.1)
+    px = (rows - 4) / 1.2
+    grid = tm.PolarGrid(R=rows, n_theta=n_theta, cx=62.0, cy=64.0)
+    lib = tm.Library(lib_np["kx"], lib_np["ky"], lib_np["intensity"], lib_np["offsets"], px, grid, fft=True)
+    info = lib.info()
+    print("pixels per row and template", info["n_spots"] / lib.n_total / lib.rows()[0], lib.layout(), flush=True)
+    assert info["n_spots"] > 24 * lib.n_total and lib.layout()["n_records"] >= 131072
+    x = torch.from_numpy(_patterns(lib_np, px, rows, 512, seed=5, H=128, W=124)).cuda()
+    every, nall, _ = tm.polar_transform(x, grid, lib=lib)
+    for B in (1, 9, 24, 25, 49, 100, 200, 512):
+        print("[case] dense", n_theta, rows, T, max_spots, "B", B, flush=True)
+        polar, norms = every[:B], nall[:B]
+        for N in (1, 5):
+            want = exhaustive(tm, lib, polar, norms, N)
+            for kw in ({}, dict(coarse="bound"), dict(coarse="fft")):
+                assert same_rows(tm.match_batch(lib, polar, norms, N, **kw), want), (B, N, kw)
     lib.free()
