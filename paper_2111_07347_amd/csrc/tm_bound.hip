@@ -124,9 +124,6 @@ constexpr int64_t kBoundRecords = 131072;  // records from which a search of a d
                                            //   scanned, 2.1 searched; 999, 52 patterns, 720 columns:
                                            //   1.0 and 2.2; 3000, 512 patterns: 0.9 searched)
 constexpr int64_t kBoundAlways = 1000000;  // and from which it always does
-constexpr int64_t kRefineRecords = 450000; // least records of a crowded one that is refined rather
-                                           //   than scanned (8 patterns, 5000 templates on 180
-                                           //   columns: 0.94, 0.38 ms; 8000: 0.40, 0.54)
 constexpr int32_t kSearchChunk = 65536;    // patterns of a plain path's search at a time, and
 constexpr size_t kSearchScratch = size_t(4) << 30;   // the bytes of their bounds
 constexpr int kFillGrid = 512;             // workgroups that fill the chip (two per CU)
@@ -136,9 +133,13 @@ constexpr int kFillGrid = 512;             // workgroups that fill the chip (two
 // on 180 columns, 32: 305, 319; 128: 864, 365). Crowded templates have too many
 // patterns without a clear best one for it, unless the batch is so small that
 // the passes are all launches (128 x 128, 11 600 templates, 3 patterns: 406,
-// 1054; 20 000, one: 1415, 930; 32: 2307, 1598; 128: 6549, 3790).
+// 1054; 20 000, one: 1415, 930; 32: 2307, 1598; 128: 6549, 3790). With 1.9 pixels
+// per touched row and template nearly all patterns are such (42 rows, 6000 on
+// 180 columns, 3 patterns: 916, 632; one: 586, 628; 64-pixel radii, 1.4: 490, 843).
 constexpr int kRefineBatch = 48;           // largest batch of a dense library that is refined,
 constexpr int kRefineCrowded = 8;          //   the same of a crowded one,
+constexpr int kRefinePacked = 2;           //   and with kPacked pixels per row and template,
+constexpr double kPacked = 1.6;
 constexpr int kRefineTemplates = 8192;     //   its least templates
 constexpr int64_t kRefineSpots = 24;       //   and pixels per template
 // Columns of a polar row: with up to two per lane a scan of a dense library is
@@ -898,10 +899,25 @@ bool searches_all(const tm_library* L, int32_t B) {
     return L->sr_all && !loose && !(many && (few_columns || n > kRefineColumns[1]));
 }
 
+double pixels_per_row(const tm_library* L) { return static_cast<double>(L->n_spots) / L->n_rows / L->Tp; }
+bool packed(const tm_library* L) { return pixels_per_row(L) > kPacked; }
+
 // Whether a dense library's bounds are refined (see kRefineBatch).
 bool refines(const tm_library* L, int32_t B) {
-    return L->search && B <= (tmlib::crowded(L) ? kRefineCrowded : kRefineBatch) && L->Tp >= kRefineTemplates &&
-           L->n_spots >= kRefineSpots * L->Tp && L->n_theta > kRefineColumns[0] && L->n_theta <= kRefineColumns[1];
+    const int most = packed(L) ? kRefinePacked : tmlib::crowded(L) ? kRefineCrowded : kRefineBatch;
+    return L->search && B <= most && L->Tp >= kRefineTemplates && L->n_spots >= kRefineSpots * L->Tp &&
+           L->n_theta > kRefineColumns[0] && L->n_theta <= kRefineColumns[1];
+}
+
+// Whether that is faster than the scan split over the chip (us, refined and
+// scanned, means over pattern sets, orthorhombic): 53 rows, 3 patterns: 6000
+// templates on 180 columns 490, 301; 12 000: 489, 743; on 360: 432, 396; 309,
+// 758; 42 rows: 8000 on 360 1140, 646; 12 000: 1035, 1095; 62 rows: 4200 on 180
+// 379, 238; 8000: 308, 377; 4200 on 360: 207, 317.
+bool refined_before_scan(const tm_library* L, int32_t B) {
+    if (!refines(L, B)) return false;
+    if (!tmlib::crowded(L)) return true;
+    return L->n_records >= (packed(L) ? 800000 : L->n_theta <= kFewColumns ? 450000 : 0);
 }
 
 }  // namespace
@@ -1033,10 +1049,9 @@ bool tmlib::search_pays(const tm_library* lib, int32_t B) {
     const double b = B, w = static_cast<double>(lib->n_records) * (1 + lib->group * slots_for(lib->n_theta));
     if (!lib->sr_all) {
         if (!bounds_pay(lib) || lib->n_records >= kBoundAlways) return bounds_pay(lib);
-        if (refines(lib, B) && !(crowded(lib) && lib->n_records < kRefineRecords)) return true;
-        const double pixels = static_cast<double>(lib->n_spots) / lib->n_rows / lib->Tp;
+        if (refined_before_scan(lib, B)) return true;
         const double records = static_cast<double>(lib->n_records);
-        return b * w * records >= 2.3e14 * (pixels - 0.8) * (lib->n_theta > kRefineColumns[1] ? 2 : 1);
+        return b * w * records >= 2.3e14 * (pixels_per_row(lib) - 0.8) * (lib->n_theta > kRefineColumns[1] ? 2 : 1);
     }
     if (lib->n_theta <= 128) return w >= 9e4 && b * w >= 2.2e8 && b * b * w >= 5e10;
     const bool large = w >= 1e5 && lib->n_spots < kManySpots * lib->Tp;
