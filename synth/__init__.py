@@ -481,7 +481,16 @@ def make_patterns_parallel(cfg: Config | int, lib: dict, n: int, workers: int = 
     with mp.get_context("fork").Pool(workers) as pool:
         for lo, arr in pool.imap_unordered(_worker, jobs):
             out[lo:lo + len(arr)] = arr
+        _end(pool)
     return out
+
+
+def _end(pool):
+    """Lets a pool's workers end by themselves. Leaving its block ends them with
+    a signal, which a profiler that is loaded into them catches and, from a
+    fork's state, may never return from."""
+    pool.close()
+    pool.join()
 
 
 # --------------------------------------------------------------------------
@@ -517,5 +526,6 @@ def serving_row(row_id: int, lib_id: int, lib: dict | None = None, workers: int 
         chunks = [list(idx)[i:i + 32] for i in range(0, SERVING_ROW, 32)]
         with mp.get_context("fork").Pool(workers) as pool:
             parts = pool.starmap(make_patterns, [(cfg, lib, c) for c in chunks])
+            _end(pool)
         return np.concatenate(parts)
     return make_patterns(cfg, lib, idx)
