@@ -1027,7 +1027,8 @@ bool tmlib::bounds_pay(const tm_library* lib) {
 // templates (w 246 thousand), 64 patterns 104, 188; 192: 201, 197; 2048: 1128,
 // 399; 8000 HCP (1.6 million), 32: 222, 382; 128: 582, 411; 2048: 6701, 1311; 300
 // FCC (55 thousand), 1024: 179, 182; 2048: 310, 243; 100 FCC, 4096: 291, 335; 300
-// HCP on 240 columns (62 thousand), 1024: 188, 287; 4096: 596, 520; 1200 FCC on
+// HCP on 240 columns (62 thousand), 1024: 188, 287; 4096: 596, 520; 216 (48
+// thousand), 2048: 258, 337; 4096: 468, 546; 1200 FCC on
 // 180 (76 thousand), 512: 182, 203; 2048: 500, 349; 2000 FCC on 90 (77
 // thousand), 4096: 1150, 1388; 6000 (210 thousand), 1024: 893, 1037; 4096: 2965,
 // 2318; 3000 HCP (216 thousand), 512: 408, 609; 1024: 682, 599.
@@ -1056,6 +1057,8 @@ bool tmlib::search_pays(const tm_library* lib, int32_t B) {
     if (lib->n_theta <= 128) return w >= 9e4 && b * w >= 2.2e8 && b * b * w >= 5e10;
     const bool large = w >= 1e5 && lib->n_spots < kManySpots * lib->Tp;
     if (lib->n_theta <= kFewColumns) return b * b * w >= 2.4e10 && (large || (w >= 6e4 && b * w >= 8e7));
+    if (lib->n_theta <= kSomeColumns && w < 1e5 && lib->n_spots >= kManySpots * lib->Tp)
+        return w >= 6e4 && b * w >= 2e8;
     return b * b * w >= 1e10 && (large || (lib->n_records >= 2500 && b * w >= 8e7));
 }
 

@@ -148,7 +148,8 @@ def test_scans_split_over_workgroups(tm, n_theta, rows, T, max_spots):
 # columns over a multiple of the windows, many pixels per template)
 @pytest.mark.parametrize("n_theta,T,max_spots,Bs", [
     (90, 2200, 8, (64, 127, 128, 700, 1500)), (72, 2200, 8, (128, 1500)), (180, 1500, 8, (300, 700, 1400)),
-    (220, 900, 34, (500, 2047, 2048)), (360, 700, 8, (60, 300, 900, 1700)), (720, 600, 34, (100, 300, 900))])
+    (220, 900, 34, (500, 2047, 2048)), (240, 170, 34, (1024, 4096)),
+    (360, 700, 8, (60, 300, 900, 1700)), (720, 600, 34, (100, 300, 900))])
 def test_sparse_libraries_by_scan_search_or_certified(tm, n_theta, T, max_spots, Bs):
     import torch
     lib, lib_np, grid = _library(tm, n_theta, T, max_spots)
